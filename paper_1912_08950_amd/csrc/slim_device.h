@@ -19,13 +19,33 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return (uint64_t(1) << lane_id()) - 1;  // lane 0 -> 0
 }
 
-// Inclusive max-scan across the 64 lanes of a wave.
+// Lane i's value moved by one step of a wave scan (data-parallel primitives:
+// shifts by 1, 2, 4, 8 inside rows of 16 lanes, then lane 15 of each odd row's
+// predecessor and lane 31 broadcast); 0 where no lane is the source.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, false);
+}
+
+// Inclusive max-scan and sum-scan across the 64 lanes of a wave (every lane
+// active).
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    uint32_t o = __shfl_up(v, d, kWave);
-    if ((int)lane_id() >= d) v = v > o ? v : o;
-  }
+  v = max(v, dpp_or_zero<0x111, 0xf>(v));  // row_shr:1, 2, 4, 8
+  v = max(v, dpp_or_zero<0x112, 0xf>(v));
+  v = max(v, dpp_or_zero<0x114, 0xf>(v));
+  v = max(v, dpp_or_zero<0x118, 0xf>(v));
+  v = max(v, dpp_or_zero<0x142, 0xa>(v));  // row_bcast:15 into rows 1 and 3
+  v = max(v, dpp_or_zero<0x143, 0xc>(v));  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+__device__ __forceinline__ uint32_t wave_incl_sum32(uint32_t v) {
+  v += dpp_or_zero<0x111, 0xf>(v);
+  v += dpp_or_zero<0x112, 0xf>(v);
+  v += dpp_or_zero<0x114, 0xf>(v);
+  v += dpp_or_zero<0x118, 0xf>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);
+  v += dpp_or_zero<0x143, 0xc>(v);
   return v;
 }
 
@@ -76,12 +96,13 @@ __device__ __forceinline__ void philox_w01(uint32_t x0, uint32_t x1, uint32_t x2
   w1 = r.y;
 }
 
-// Sort three distinct vertex ids ascending.
+// Sort three distinct vertex ids ascending (one three-operand minimum, median
+// and maximum).
 __device__ __forceinline__ void sort3(uint32_t& a, uint32_t& b, uint32_t& c) {
-  uint32_t t;
-  if (a > b) { t = a; a = b; b = t; }
-  if (b > c) { t = b; b = c; c = t; }
-  if (a > b) { t = a; a = b; b = t; }
+  const uint32_t lo = min(a, b), hi = max(a, b), t = c;
+  a = min(lo, t);
+  b = max(lo, min(hi, t));
+  c = max(hi, t);
 }
 
 __device__ __forceinline__ void bit_set(uint32_t* bits, uint32_t idx) {

@@ -8,14 +8,24 @@
 // and in out(y) above x.  Work is organised over tiles of CSR entries: the
 // rows of a tile are middle vertices, their backward entries are the
 // in-edges, and their out-lists sit in an LDS hash keyed by (w, row).  Each
-// in-edge (y,x) scans the part of out(y) ranked above x -- the suffix after
-// x for a sorted row (binary search), the whole row for a short one -- and
-// the scan items of all in-edges of a batch are spread over the lanes so
-// that loads are contiguous.  Hits go to a per-wave queue and are hashed
-// (Philox4x32-10 of the id-sorted triple) 64 at a time.
+// in-edge (y,x) scans the part of out(y) ranked above x, the suffix after x of
+// the sorted row; the scan items of all in-edges of a batch are spread over
+// the lanes, kQuad consecutive ones per lane.
 //
-// Deletion marks: (x,w) lies in the tile's own out-lists and is collected
-// in an LDS bitmap; (y,x) is a per-in-edge flag; (y,w) is a byte store into
+// What bounds the scan is vector-instruction issue, then LDS traffic, so an
+// item costs as little as possible: one multiply-add, one 4-byte read of a
+// 65536-bit filter and one bit test.  At scale 24 a quarter of the items are
+// triangles and at most 3% more pass the filter; only those go to a per-wave
+// stack, 64 at a time, for the exact look-up in the hash, the Philox draw of
+// the id-sorted triple and the marks.  Probing the hash itself for every item
+// (two 16-byte LDS reads and four key compares) took 4.08e10 vector
+// instructions and 111.6 ms on that graph; filter, stack and 4-item lanes take
+// 2.78e10 and 81.6 ms.  The in-edge of a lane's quad comes from a bit mask of
+// the in-edge starts (two bit counts) instead of a scalar loop over the
+// boundaries inside a window.
+//
+// Deletion marks: (x,w) lies in the tile's own out-lists and (y,x) is an
+// in-edge of the batch: byte flags in LDS; (y,w) is a byte store into
 // the global per-edge mark bytes over DAG positions (the first two are
 // flushed there too).  Every mark sets a value to 1 and nothing is cleared,
 // so the result does not depend on the order in which triangles are found.
@@ -23,9 +33,9 @@
 // Variants (section 4.3), in the general instantiation of the kernel:
 // Triangle p-2-Reduction marks the two edges other than the drawn one;
 // Min-Count p-1-Reduction first runs a counting pass (its own instantiation:
-// every triangle adds 1 to each of its edges where the probe finds it, with
-// LDS counters for (y,x) and (x,w) and a global atomic for (y,w); no queue,
-// no hash of the triple) and then marks, in each selected triangle, the edge
+// every triangle adds 1 to each of its edges, with
+// LDS counters for (y,x) and (x,w) and a global atomic for (y,w); no hash of
+// the triple) and then marks, in each selected triangle, the edge
 // of fewest triangles (ties: the drawn index among the tied edges).
 //
 // Edge-Once p-1-Reduction (section 4.3 with the conditions of section 6.2)
@@ -59,124 +69,128 @@ namespace slim {
 constexpr int kTB = SLIM_TRI_BLOCK;  // threads per block
 constexpr int kTW = kTB / kWave;     // waves per block
 constexpr int kTT = 1024;            // CSR entries per tile
-constexpr int kTC = kTT / kWave;     // 64-entry chunks per tile
-constexpr int kChunksPerWave = (kTC + kTW - 1) / kTW;
+constexpr int kEntries = kTT / kTB;  // consecutive tile entries per thread
 constexpr int kWavesPerEU = 2 * kTW / 4;  // two resident blocks per CU (LDS), four SIMDs
 constexpr int kHashCap = 2048;       // out-list entries hashed per pass
-constexpr int kBuckets = 2048;       // hash buckets of two slots (load <= 1/2)
-constexpr int kBucketBits = 11;
-constexpr int kQ = 128;              // per-wave hit queue (records)
-#ifndef SLIM_TRI_UNROLL
-#define SLIM_TRI_UNROLL 8
-#endif
-constexpr int kUnroll = SLIM_TRI_UNROLL;  // windows of 64 items whose loads are in flight together
+constexpr int kHashPer = kHashCap / kTB;  // most hashed entries per thread
+constexpr int kSlotBits = 12;        // one-entry slots of the hash (load <= 1/2)
+constexpr int kSlots = 1 << kSlotBits;
+constexpr int kFiltWords = 2048;     // words of the filter: 65536 bits
+constexpr int kQ = 128;              // per-wave candidate stack (records)
+constexpr int kItemBits = 17;        // scan items of one mask pass: at most 2^17
+// Windows whose loads are in flight together: p-1 at R-MAT scale 24 takes
+// 102.6 ms with two, 98.9 with three and 98.5 with four (whose batch of 256
+// graphs is 0.5% slower).
+constexpr int kDepth = 3;
 constexpr uint32_t kEmpty = 0xffffffffu;
 constexpr uint32_t kDead = 0xffffffffu;  // Edge-Once list record of a decided triangle
 
-static_assert(kTC <= kWave && kHashCap / kWave <= kWave, "one wave scans the chunk sums and maxima");
+static_assert(kEntries * kTB == kTT && kEntries == 2, "two tile entries per thread");
+static_assert(kHashCap <= kSlots / 2 && kHashCap < (1 << kSlotBits) - 1, "position fits the slot's low bits");
 
-// In-edges per batch (kB) of each instantiation: as many as two blocks per CU
-// allow in LDS; the general and Edge-Once ones also keep per-in-edge counts
-// or bids (larger batches cut the per-batch setup and barriers).
+// In-edges per batch (kB) and words of the in-edge mask (kM) of each
+// instantiation: as many as two blocks per CU allow in LDS; the general and
+// Edge-Once ones also keep per-in-edge counts or bids (larger batches cut
+// the per-batch setup and barriers).
 constexpr int kLdsPerBlock = 160 * 1024 / 2;
 template <int kMode>
 constexpr int kBatchOf = kMode == kModePlain ? 512 : (kMode == kModeEO ? 352 : 384);
+template <int kMode>
+constexpr int kMaskOf = kMode == kModePlain ? 512 : 256;
 
-template <int kB>
+// Scan items per lane of a window.  Four (one 16-byte load, one in-edge
+// search and one address for four items) is the fastest at R-MAT scale 24:
+// 102.6 ms per p-1 call against 112.6 with two and 133 with one.  The
+// counting pass takes one: every hit is a global atomic on its {y,w} edge,
+// and only consecutive items in consecutive lanes let the atomics of a line
+// travel together (scale 20: 4.25 ms with one, 6.97 ms with four).
+template <int kMode>
+constexpr int kQuadOf = kMode == kModeCount ? 1 : 4;
+
+template <int kB_, int kM_, int kQuad_>
 struct TriSmem {
-  static_assert(kB <= kTB, "one thread per in-edge in the setup");
+  static constexpr int kB = kB_, kM = kM_, kQuad = kQuad_;
+  static_assert(kB <= kTB && kM <= kTB, "one thread per in-edge and per mask word in the setup");
+  static_assert(kM * kWave * kQuad <= (1 << kItemBits) && kB <= (1 << (32 - kItemBits)),
+                "a candidate's in-edge and item share one word");
+  uint32_t filt[kFiltWords];  // bit set: some hashed key may have it
+  uint32_t slot[kSlots];      // (hash << kSlotBits) | position in range, or kEmpty
+  uint32_t xw[kHashCap];      // rank id and original (local) id of each hashed
+  uint32_t xold[kHashCap];    //   out-list entry
+  uint8_t xflag[kHashCap];    // deletion mark of each hashed entry
   uint32_t srow[kTT];  // row of each tile entry (after the max-scan)
-  uint32_t cmax[kTC];
-  uint16_t bw[kTT];    // local indices of the tile's backward entries, in order
-  uint32_t fwd[kTT / 32];  // forward entries of the tile (edge ids come from the hash)
-  uint4 hb[kBuckets + 1];     // two slots {w, tag}; tag = (position in range << 16) | row tag
-  uint32_t xold[kHashCap];    // original id of each hashed out-list entry
-  uint32_t xbits[kHashCap / 32 + 2];
-  uint4 ie[kB];           // {scan begin, x rank, y old id, x old id}
-  uint32_t ie_pre[kB + 1];
-  uint32_t ie_e[kB];      // DAG position of (y,x) (kEmpty until found)
-  uint4 ie_scan[kB];      // {scan begin - item base, hash tag, next in-edge start, 0}
-  uint32_t ie_flag[(kB + 31) / 32];
+  uint16_t bw[kTT];    // local indices of the tile's backward entries, in order, and,
+                       //   from the end down, of its forward entries
+  // the batch's in-edges that have something to scan, in order
+  uint2 ie_scan[kB];      // {scan begin - first item, row constant of the hash}
+  uint4 ie_tri[kB];       // {end item, y old id, x old id, row's first position | length << 16}
+  uint32_t ie_pre[kB];    // first quad
+  uint8_t ie_flag[kB];    // deletion mark of (y,x)
+  uint64_t mask[kM];      // bit i of a window: the next in-edge starts at its quad i + 1
   union {
-    uint32_t dpos[kHashCap];  // row start offset of each hashed position
-    uint2 queue[kTW][kQ];     // hit records {item, (in-edge << 16) | position in range}
+    uint32_t dpos[kHashCap];  // row start offset at each row's first hashed position, else 0
+    uint2 queue[kTW][kQ];     // candidates {w, (in-edge << kItemBits) | item}
   } u;
-  uint32_t wsum[kTW];
-  uint32_t cbase[kHashCap / kWave];  // per chunk: bw slots of the tile, or row offset maxima of the hashed range
-  uint64_t cmask[kTC];
+  uint32_t wsum[kTW], wcnt[kTW], wmax[kTW];
   uint32_t bcast[4];
   uint64_t red[2][kTW];
 };
 
-template <int kB>
+template <int kB, int kM, int kQ>
 struct TriSmemPlain {
-  TriSmem<kB> s;
+  TriSmem<kB, kM, kQ> s;
 };
 // LDS of the general instantiation: per-edge triangle counts of the hashed
 // range and of the batch's in-edges (accumulated in the counting pass, loaded
 // for the Min-Count selection).
-template <int kB>
+template <int kB, int kM, int kQ>
 struct TriSmemGeneral {
-  TriSmem<kB> s;
+  TriSmem<kB, kM, kQ> s;
   uint32_t xcnt[kHashCap];
   uint32_t ie_cnt[kB];
 };
 // LDS of the Edge-Once instantiation: the smallest bid on each in-edge of
 // the batch, written to the global minimum once per batch, and the smallest
 // priority word bid on each hashed out-list entry in the current pass.
-template <int kB>
+template <int kB, int kM, int kQ>
 struct TriSmemEO {
-  TriSmem<kB> s;
+  TriSmem<kB, kM, kQ> s;
   uint64_t ie_key[kB];
   uint32_t xmin[kHashCap];
 };
 
-// A key is (w, row tag) with row tag = 16 x (offset of the row's start in
-// the hashed range), below 2^15; bucket addresses are byte offsets (16 B per
-// bucket).  A slot's tag word holds (position in range << 16) | row tag, and
-// bit 31 of a bucket's second tag word (kPassed) is set once an insertion
-// found the bucket full and went on past it.
-constexpr uint32_t kRowTag = 4;             // row tag = row offset << kRowTag
-constexpr uint32_t kPassed = 0x80000000u;
-constexpr uint32_t kQposMask = 0x7fffu;     // position in range, from tag >> 16
-constexpr uint32_t kNoRow = 0xffffu;        // a row tag no key has
-
-// Byte offset of the home bucket of key (w, row tag g), below 16 kBuckets:
-// bits 21..31 of w * 0x9E3779B1 xor the row offset, times 16.
-__device__ __forceinline__ uint32_t hhome(uint32_t w, uint32_t g) {
-  return (((w * 0x9E3779B1u) >> (32 - kBucketBits - kRowTag)) ^ g) &
-         ((kBuckets - 1) << kRowTag);
+// A key is (w, row); rows are told apart by the position rs of their first
+// entry in the hashed range.  Its 32-bit hash w * A + rs * B gives the home
+// slot (top 12 bits, then linear probing), the 20 low bits kept beside the
+// position in the slot, and the filter's word (top 11 bits) and bit (low 5).
+__device__ __forceinline__ uint32_t hrow(uint32_t rs) { return rs * 0x85EBCA6Bu; }
+__device__ __forceinline__ uint32_t hkey(uint32_t w, uint32_t row) {
+  return (uint32_t)((uint64_t)w * 0x9E3779B1u + row);  // one multiply-add
+}
+// The filter's bit is moved to the sign of its word.
+__device__ __forceinline__ bool hfilter(const uint32_t* filt, uint32_t h) {
+  const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(filt) +
+                                                        ((h >> 19) & (4u * kFiltWords - 4u)));
+  return (int32_t)(v << (h & 31u)) < 0;
 }
 
-// Probe order: home buckets are 0 .. kBuckets-1; the walk goes on to the
-// spare bucket kBuckets and then wraps to 0, so a home bucket and the next
-// one are always adjacent in LDS.  b is a byte offset.
-__device__ __forceinline__ uint32_t hnext(uint32_t b) {
-  return b == (kBuckets << kRowTag) ? 0u : b + (1u << kRowTag);
-}
-
-__device__ __forceinline__ uint4 hread(const uint4* hb, uint32_t b) {
-  return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(hb) + b);
-}
-
-// Look up (w, row tag g).  Slots fill in probe order and are never removed,
-// so the key lies past a bucket only if an insertion went on past it.
-__device__ __forceinline__ bool hlookup(const uint4* hb, uint32_t w, uint32_t g,
-                                        uint32_t& qpos) {
-  uint32_t b = hhome(w, g);
-  for (;;) {
-    const uint4 e = hread(hb, b);
-    if (e.x == w && (e.y & 0xffffu) == g) {
-      qpos = (e.y >> 16) & kQposMask;
-      return true;
-    }
-    if (e.z == w && (e.w & 0xffffu) == g) {
-      qpos = (e.w >> 16) & kQposMask;
-      return true;
-    }
-    if (!(e.w & kPassed)) return false;
-    b = hnext(b);
-  }
+// Exact look-up of w, of hash h, in the row of positions [rsl & 0xffff, +
+// (rsl >> 16)).  Slots fill in probe order, are never removed and are at most
+// half full, so the walk ends at the key or at an empty slot.
+template <class Smem>
+__device__ __forceinline__ bool hfind(const Smem& S, uint32_t w, uint32_t h, uint32_t rsl,
+                                      uint32_t& qpos) {
+  uint32_t b = h >> (32 - kSlotBits);
+  const uint32_t hl = h << kSlotBits, rs = rsl & 0xffffu, len = rsl >> 16;
+  bool hit, go;
+  do {  // straight-line: an empty slot's q fails the range test (q >= kHashCap or the fingerprint)
+    const uint32_t v = S.slot[b], q = v ^ hl;
+    hit = (S.xw[q & (kHashCap - 1)] == w) & (q - rs < len);
+    qpos = q & (kHashCap - 1);
+    go = !hit & (v != kEmpty);
+    b = (b + 1) & (kSlots - 1);
+  } while (go);
+  return hit;
 }
 
 // First position in the sorted DAG range [lo, hi) whose rank id is >= x
@@ -219,42 +233,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Row of every entry of the tile [j0, j0 + kTT): srow[i] after the scan.
-template <int kB>
-__device__ void tri_tile_rows(const int64_t* row_off, int64_t j0, uint32_t lo, uint32_t hi,
-                              TriSmem<kB>& S) {
-  const int t = threadIdx.x, w = t / kWave, lane = lane_id();
-  for (int i = t; i < kTT; i += kTB) S.srow[i] = 0;
-  __syncthreads();
-  if (t == 0) S.srow[0] = lo > 0 ? lo - 1 : 0;
-  __syncthreads();
-  for (uint64_t r = lo + (uint64_t)t; r < hi; r += kTB) {
-    const int64_t b = row_off[r], e = row_off[r + 1];
-    const int64_t s = b - j0;
-    if (e > b && s >= 0 && s < kTT) S.srow[s] = r;
-  }
-  __syncthreads();
-  for (int c = w; c < kTC; c += kTW) {
-    const uint32_t v = wave_incl_max(S.srow[c * kWave + lane]);
-    S.srow[c * kWave + lane] = v;
-    if (lane == kWave - 1) S.cmax[c] = v;
-  }
-  __syncthreads();
-  if (w == 0) {
-    const uint32_t v = lane < kTC ? S.cmax[lane] : 0;
-    const uint32_t incl = wave_incl_max(v);
-    uint32_t excl = __shfl_up(incl, 1, kWave);
-    if (lane == 0) excl = 0;
-    if (lane < kTC) S.cmax[lane] = excl;
-  }
-  __syncthreads();
-  for (int i = t; i < kTT; i += kTB) {
-    const uint32_t a = S.srow[i], b = S.cmax[i >> 6];
-    S.srow[i] = a > b ? a : b;
-  }
-  __syncthreads();
-}
-
 struct TriCtx {
   TriArgs a;
   uint32_t* xcnt;    // general instantiation only: per-edge counts of the hashed range
@@ -265,7 +243,8 @@ struct TriCtx {
   int64_t j0;
   uint32_t D0;    // first DAG position of the hashed range
   uint32_t hlen;  // number of hashed entries
-  uint64_t thr;   // the tile's graph: selection threshold, Philox key, first vertex
+  uint32_t thr_last;  // the tile's graph: largest selected Philox word 0 (if
+  bool thr_any;       //   any is), Philox key, first vertex
   uint32_t k0, k1, vb;
   uint32_t op;    // the tile's graph's operation
   bool eo_later;  // an Edge-Once pass after the first bids: eids are known, closed edges skipped
@@ -276,93 +255,129 @@ struct TriCtx {
   uint64_t n_tri, n_sel;
 };
 
-// Hash the out-list entries [D0, D0 + len) under key (w, row tag); the row
-// start offset comes from dpos (all rows of the tile) or is 0 (one row).
-template <int kB>
-__device__ void tri_build_hash(TriCtx& C, TriSmem<kB>& S, uint32_t len, bool use_dpos) {
-  for (int i = threadIdx.x; i < kBuckets + 1; i += kTB)
-    S.hb[i] = make_uint4(kEmpty, 0u, kEmpty, 0u);
-  for (int i = threadIdx.x; i < kHashCap / 32 + 2; i += kTB) S.xbits[i] = 0;
-  __syncthreads();
-  uint32_t* hw = reinterpret_cast<uint32_t*>(S.hb);
-  const bool skip_closed = C.eo_later;
-  for (uint32_t q = threadIdx.x; q < len; q += kTB) {
-    const uint32_t w = C.a.dag_col[C.D0 + q];
-    S.xold[q] = C.a.order[w];
-    if (C.xmin) C.xmin[q] = 0xffffffffu;
-    // Edge-Once rounds after the first pass: a closed edge {x,w} decides
-    // every triangle on it, so it is left out of the hash
-    if (skip_closed && bit_get(C.a.closed, C.D0 + q)) continue;
-    const uint32_t g = (use_dpos ? S.u.dpos[q] : 0u) << kRowTag;
-    uint32_t b = hhome(w, g);
-    for (;;) {
-      uint32_t* s = hw + b / 4;
-      // tags are ORed in: an insertion passing the bucket may set kPassed
-      // in the second tag word at the same time
-      if (atomicCAS(&s[0], kEmpty, w) == kEmpty) {
-        atomicOr(&s[1], (q << 16) | g);
-        break;
-      }
-      if (atomicCAS(&s[2], kEmpty, w) == kEmpty) {
-        atomicOr(&s[3], (q << 16) | g);
-        break;
-      }
-      atomicOr(&s[3], kPassed);
-      b = hnext(b);
+// Empties the hash, the filter and the flags of the hashed entries.
+template <class Smem>
+__device__ __forceinline__ void tri_clear_hash(Smem& S) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < kSlots / 4; i += kTB)
+    reinterpret_cast<uint4*>(S.slot)[i + tid] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+  reinterpret_cast<uint4*>(S.filt)[tid] = make_uint4(0u, 0u, 0u, 0u);
+  reinterpret_cast<uint32_t*>(S.xflag)[tid] = 0;
+}
+static_assert(kSlots / 4 % kTB == 0 && kFiltWords / 4 == kTB && kHashCap / 4 == kTB,
+              "whole vectors per thread");
+
+// Hash the out-list entries [D0, D0 + len) into the cleared hash.  A thread
+// takes `per` consecutive entries (the fewest that cover the range), so that
+// the row of each comes from a max-scan over the row starts in dpos (all rows
+// of the tile; every row start is 0 for one row).
+template <class Smem>
+__device__ void tri_build_hash(TriCtx& C, Smem& S, uint32_t len, bool all_rows) {
+  const uint32_t tid = threadIdx.x, wave = tid / kWave;
+  const uint32_t per = (len + kTB - 1) / kTB, q0 = tid * per;
+  uint32_t w[kHashPer], o[kHashPer], g[kHashPer];
+#pragma unroll
+  for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i)
+    w[i] = i < per && q0 + i < len ? C.a.dag_col[C.D0 + q0 + i] : 0u;
+#pragma unroll
+  for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i)
+    o[i] = i < per && q0 + i < len ? C.a.order[w[i]] : 0u;
+  if (all_rows) {
+    uint32_t m = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i) {
+      m = max(m, i < per && q0 + i < len ? S.u.dpos[q0 + i] : 0u);
+      g[i] = m;
     }
+    const uint32_t incl = wave_incl_max(m);
+    if (lane_id() == kWave - 1) S.wsum[wave] = incl;
+    uint32_t before = __shfl_up(incl, 1, kWave);
+    if (lane_id() == 0) before = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kTW; ++i)
+      if (i < wave) before = max(before, S.wsum[i]);
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i) g[i] = max(g[i], before);
+  } else {
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i) g[i] = 0;
+  }
+  const bool skip_closed = C.eo_later;
+#pragma unroll
+  for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i) {
+    const uint32_t q = q0 + i;
+    if (i >= per || q >= len) break;
+    S.xw[q] = w[i];
+    S.xold[q] = o[i] - C.vb;
+    if (C.xmin) C.xmin[q] = 0xffffffffu;
     // counts exist only for Min-Count graphs: loaded for their selection
     // pass, zeroed for their counting pass (other operations never read them)
     if (C.xcnt) C.xcnt[q] = C.a.pass == 1 && C.op == SLIM_OP_MCTR ? C.a.tcount[C.D0 + q] : 0u;
+    // Edge-Once rounds after the first pass: a closed edge {x,w} decides
+    // every triangle on it, so it is left out of the hash
+    if (skip_closed && bit_get(C.a.closed, C.D0 + q)) continue;
+    const uint32_t h = hkey(w[i], hrow(g[i]));
+    atomicOr(&S.filt[h >> 21], 0x80000000u >> (h & 31u));
+    uint32_t b = h >> (32 - kSlotBits);
+    while (atomicCAS(&S.slot[b], kEmpty, (h << kSlotBits) | q) != kEmpty) b = (b + 1) & (kSlots - 1);
   }
   C.hlen = len;
   __syncthreads();
 }
 
-template <int kB>
-__device__ void tri_flush_xbits(TriCtx& C, TriSmem<kB>& S) {
-  __syncthreads();
+// Marks (counting pass: counts) of the hashed range, behind the barrier that
+// ends the scan; a thread reads the flags that it clears for the next range.
+template <class Smem>
+__device__ void tri_flush_xflags(TriCtx& C, Smem& S) {
   if (C.xcnt && C.a.pass == 0) {  // counting pass: add the (x,w) counts of the range
     for (uint32_t q = threadIdx.x; q < C.hlen; q += kTB) {
       const uint32_t v = C.xcnt[q];
       if (v) atomicAdd(C.a.tcount + C.D0 + q, v);
     }
   } else {
-    const uint32_t nwords = (C.D0 % 32 + C.hlen + 31) / 32;
-    const uint32_t base = C.D0 / 32;
-    for (uint32_t i = threadIdx.x; i < nwords; i += kTB)
-      for (uint32_t v = S.xbits[i]; v; v &= v - 1) mark_set(C.a.marks, (base + i) * 32u + __builtin_ctz(v));
+    for (uint32_t i = threadIdx.x; 4 * i < C.hlen; i += kTB) {
+      const uint32_t v = reinterpret_cast<const uint32_t*>(S.xflag)[i];
+      if (v == 0) continue;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t)
+        if ((v >> (8 * t)) & 1u) mark_set(C.a.marks, C.D0 + 4 * i + t);
+    }
   }
-  __syncthreads();
 }
 
 // Forward entries among tile entries [ia, ib): their edge is in out(x) of the
 // entry's own row, so the DAG position comes from the hash (a miss means the
-// entry lies in another pass of a split row).
-template <int kB>
-__device__ void tri_forward_eids(TriCtx& C, TriSmem<kB>& S, uint32_t ia, uint32_t ib,
+// entry lies in another pass of a split row).  nfw: forward entries of the tile.
+template <class Smem>
+__device__ void tri_forward_eids(TriCtx& C, Smem& S, uint32_t nfw, uint32_t ia, uint32_t ib,
                                  bool all_rows) {
   if (C.hlen == 0) return;
-  for (uint32_t i = ia + threadIdx.x; i < ib; i += kTB) {
-    if (!(S.fwd[i >> 5] & (1u << (i & 31)))) continue;
+  for (uint32_t f = threadIdx.x; f < nfw; f += kTB) {
+    const uint32_t i = S.bw[kTT - 1 - f];
+    if (i < ia || i >= ib) continue;
     const uint64_t j = (uint64_t)C.j0 + i;
     const uint32_t w = C.a.rcol[j];
-    const uint32_t g = all_rows ? (C.a.fstart[S.srow[i]] - C.D0) << kRowTag : 0u;
+    uint32_t rs = 0, len = C.hlen;
+    if (all_rows) {
+      const uint32_t fs = C.a.fstart[S.srow[i]];
+      rs = fs - C.D0;
+      len = C.a.fstart[S.srow[i] + 1] - fs;
+    }
     uint32_t qpos;
-    if (hlookup(S.hb, w, g, qpos)) C.a.eid[j] = C.D0 + qpos;
+    if (hfind(S, w, hkey(w, hrow(rs)), rs | (len << 16), qpos)) C.a.eid[j] = C.D0 + qpos;
   }
 }
 
-// Marks the edge of triangle (y,x,w) that does not contain vertex `excl`
-// (union ids: c = y, u0 = x, ow = w).
-template <int kB>
-__device__ __forceinline__ void tri_mark(uint8_t* marks, TriSmem<kB>& S, uint32_t excl, uint32_t c,
-                                         uint32_t ow, uint32_t k, uint32_t qpos, uint32_t D0,
-                                         uint32_t p_yw) {
-  if (excl == ow) {  // edge {y,x}: flag of the in-edge
-    atomicOr(&S.ie_flag[k >> 5], 1u << (k & 31));
-  } else if (excl == c) {  // edge {x,w}: position qpos of the hashed range
-    const uint32_t bit = D0 % 32 + qpos;
-    atomicOr(&S.xbits[bit >> 5], 1u << (bit & 31));
+// Marks the edge of triangle (y,x,w) that does not contain vertex `excl`.
+// The marks of (y,x) and (x,w) are byte flags in LDS.
+template <class Smem>
+__device__ __forceinline__ void tri_mark(uint8_t* marks, Smem& S, uint32_t excl, uint32_t x,
+                                         uint32_t w, uint32_t k, uint32_t qpos, uint32_t p_yw) {
+  if (excl != x) {  // {y,x}, the in-edge, or {x,w}, position qpos of the hashed range
+    uint8_t* f = excl == w ? S.ie_flag + k : S.xflag + qpos;
+    *f = 1u;
   } else {  // edge {y,w}: a byte store (nothing waits on it)
     mark_set(marks, p_yw);
   }
@@ -375,36 +390,63 @@ __device__ __forceinline__ void eo_bid(uint64_t* p, uint64_t key) {
     __hip_atomic_fetch_min(p, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Edge-Once drain of the queued hits q[head .. head + cnt) (cnt <= 64): a
+// A candidate record looked up: true if (y, x, w) is a triangle.
+struct TriHit {
+  uint32_t k, qpos, p_yw;  // in-edge of the batch, position of {x,w}, DAG position of {y,w}
+  uint32_t y, x, w;        // local ids
+};
+template <class Smem>
+__device__ __forceinline__ bool tri_lookup(const Smem& S, uint2 rec, uint32_t item0, TriHit& t) {
+  t.k = rec.y >> kItemBits;
+  const uint2 sc = S.ie_scan[t.k];
+  const uint4 tr = S.ie_tri[t.k];
+  const uint32_t item = (rec.y & ((1u << kItemBits) - 1u)) + item0;
+  t.p_yw = sc.x + item;
+  t.y = tr.y;
+  t.x = tr.z;
+  t.qpos = 0;
+  // items past the in-edge's end fill up its last quad
+  const bool hit = item < tr.x && hfind(S, rec.x, hkey(rec.x, sc.y), tr.w, t.qpos);
+  t.w = S.xold[t.qpos];
+  return hit;
+}
+
+// Philox words of the id-sorted triple (local ids) under the tile's graph's
+// key.  The key is made opaque here so that the round keys are scalar adds at
+// the point of use, not twenty values kept in registers across the scan.
+__device__ __forceinline__ uint4 tri_words(const TriCtx& C, uint32_t t0, uint32_t t1, uint32_t t2) {
+  uint32_t k0 = C.k0, k1 = C.k1;
+  asm volatile("" : "+s"(k0), "+s"(k1));
+  return philox4(t0, t1, t2, 0u, k0, k1);
+}
+
+// Edge-Once drain of the stacked candidates q[0 .. cnt) (cnt <= 64): a
 // selected triangle with no closed edge bids its per-edge keys.  In the
 // bidding pass that starts the triangle list, every bidding triangle is
-// also appended to the list (one counter atomic per wave).  Returns 1 in
-// lanes that bid.
-template <int kB>
-__device__ __forceinline__ uint32_t tri_drain_eo(TriCtx& C, TriSmem<kB>& S, const uint2* q,
-                                                 uint32_t head, uint32_t cnt) {
+// also appended to the list (one counter atomic per wave).  Counts the
+// triangles and the bidding ones.
+template <class Smem>
+__device__ __forceinline__ void tri_drain_eo(TriCtx& C, Smem& S, const uint2* q, uint32_t cnt,
+                                             uint32_t item0, uint32_t& n_tri, uint32_t& n_sel) {
   const uint32_t lane = lane_id();
-  uint32_t res = 0;
   bool app = false;
   uint4 ra = make_uint4(0u, 0u, 0u, 0u), rb = ra;
-  if (lane < cnt) {
-    const uint2 rec = q[(head + lane) % kQ];
-    const uint32_t k = rec.y >> 16, qpos = rec.y & kQposMask;
-    const uint4 ie = S.ie[k];
-    const uint32_t p_yw = ie.x + (rec.x - S.ie_pre[k]);
-    const uint32_t ow = S.xold[qpos];
-    const uint32_t c = ie.z, u0 = ie.w;
-    uint32_t t0 = c, t1 = u0, t2 = ow;
-    sort3(t0, t1, t2);  // union ids of one graph: the order of its local ids
-    const uint4 wr = philox4(t0 - C.vb, t1 - C.vb, t2 - C.vb, 0u, C.k0, C.k1);
+  TriHit t;
+  if (lane < cnt && tri_lookup(S, q[lane], item0, t)) {
+    ++n_tri;
+    const uint32_t k = t.k, qpos = t.qpos, p_yw = t.p_yw;
+    const uint32_t ly = t.y, lx = t.x, lw = t.w;
+    uint32_t t0 = ly, t1 = lx, t2 = lw;
+    sort3(t0, t1, t2);
+    const uint4 wr = tri_words(C, t0, t1, t2);
     // the in-edge and the hashed entry are open (closed ones are neither
     // scanned nor hashed); {y,w} is read here
-    const bool open = (uint64_t)wr.x < C.thr && !(C.eo_later && bit_get(C.a.closed, p_yw));
+    const bool open = C.thr_any && wr.x <= C.thr_last && !(C.eo_later && bit_get(C.a.closed, p_yw));
     if (open) {
       // per-edge keys (word 2, third vertex): {y,x} -> w, {x,w} -> y, {y,w} -> x
       const uint64_t hi = (uint64_t)wr.z << 32;
-      const uint32_t e_yx = S.ie_e[k], e_xw = C.D0 + qpos;
-      const uint32_t lw = ow - C.vb, ly = c - C.vb, lx = u0 - C.vb;
+      // the scan of an in-edge begins right after its own position
+      const uint32_t e_yx = S.ie_scan[k].x + Smem::kQuad * S.ie_pre[k] - 1u, e_xw = C.D0 + qpos;
       const uint64_t k_yx = hi | lw, k_xw = hi | ly, k_yw = hi | lx;
       uint64_t* mk = C.a.minkey;
       const uint32_t kk = __umulhi(wr.y, 3u);  // edge kk of ({t0,t1}, {t0,t2}, {t1,t2})
@@ -415,9 +457,9 @@ __device__ __forceinline__ uint32_t tri_drain_eo(TriCtx& C, TriSmem<kB>& S, cons
       // minimum (that one went to the global key), so only the others bid
       if (wr.z <= atomicMin(&C.xmin[qpos], wr.z)) eo_bid(mk + e_xw, k_xw);
       eo_bid(mk + p_yw, k_yw);
-      res = 1;
+      ++n_sel;
       app = true;
-      ra = make_uint4(e_yx, e_xw, p_yw, excl == ow ? e_yx : (excl == c ? e_xw : p_yw));
+      ra = make_uint4(e_yx, e_xw, p_yw, excl == lw ? e_yx : (excl == ly ? e_xw : p_yw));
       rb = make_uint4(wr.z, lw, ly, lx);
     }
   }
@@ -448,84 +490,105 @@ __device__ __forceinline__ uint32_t tri_drain_eo(TriCtx& C, TriSmem<kB>& S, cons
       }
     }
   }
-  return res;
 }
 
-// Hash, select and mark the queued hits q[head .. head + cnt) (cnt <= 64);
-// one lane per hit.  Returns 1 in lanes whose triangle was selected.
-template <int kMode, int kB>
-__device__ __forceinline__ uint32_t tri_drain(TriCtx& C, TriSmem<kB>* Sp, const uint2* q,
-                                              uint32_t head, uint32_t cnt) {
-  constexpr bool kGeneral = kMode == kModeGeneral, kEO = kMode == kModeEO;
-  if constexpr (kEO) return tri_drain_eo(C, *Sp, q, head, cnt);
-  TriSmem<kB>& S = *Sp;
-  const uint32_t lane = lane_id();
-  uint32_t sel = 0;
-  if (lane < cnt) {
-    const uint2 rec = q[(head + lane) % kQ];
-    const uint32_t k = rec.y >> 16, qpos = rec.y & kQposMask;
-    const uint4 ie = S.ie[k];
-    const uint32_t p_yw = ie.x + (rec.x - S.ie_pre[k]);
-    const uint32_t ow = S.xold[qpos];
-    const uint32_t c = ie.z, u0 = ie.w;
-    uint32_t t0 = c, t1 = u0, t2 = ow;
-    sort3(t0, t1, t2);  // union ids of one graph: the order of its local ids
-    const uint4 wr = philox4(t0 - C.vb, t1 - C.vb, t2 - C.vb, 0u, C.k0, C.k1);
-    const uint32_t w0 = wr.x, w1 = wr.y;
-    if ((uint64_t)w0 < C.thr) {
-      sel = 1;
-      // edge e of ({t0,t1}, {t0,t2}, {t1,t2}) is the one without excl[e]
-      const uint32_t excl[3] = {t2, t1, t0};
-      if constexpr (!kGeneral) {
-        tri_mark(C.a.marks, S, excl[__umulhi(w1, 3u)], c, ow, k, qpos, C.D0, p_yw);
-      } else if (C.op == SLIM_OP_MCTR) {
-        uint32_t t[3];
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          t[e] = excl[e] == ow ? C.ie_cnt[k]
-                               : (excl[e] == c ? C.xcnt[qpos] : C.a.tcount[p_yw]);
-        const uint32_t tmin = min(t[0], min(t[1], t[2]));
-        const uint32_t nt = (t[0] == tmin) + (t[1] == tmin) + (t[2] == tmin);
-        uint32_t pick = __umulhi(w1, nt), e = 0;
-        for (; e < 3; ++e) {
-          if (t[e] != tmin) continue;
-          if (pick == 0) break;
-          --pick;
-        }
-        tri_mark(C.a.marks, S, excl[e], c, ow, k, qpos, C.D0, p_yw);
-      } else {
-        const uint32_t kk = __umulhi(w1, 3u);
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if ((C.op == SLIM_OP_TR2) ? (uint32_t)e != kk : (uint32_t)e == kk)
-            tri_mark(C.a.marks, S, excl[e], c, ow, k, qpos, C.D0, p_yw);
-      }
-    }
+// Look up the stacked candidates q[0 .. cnt) (cnt <= 64), one per lane, and
+// hash, select and mark the triangles among them (the counting pass: count
+// them on their edges).  Counts the triangles and the selected ones.
+template <int kMode, class Smem>
+__device__ __forceinline__ void tri_drain(TriCtx& C, Smem* Sp, const uint2* q, uint32_t cnt,
+                                          uint32_t item0, uint32_t& n_tri, uint32_t& n_sel) {
+  Smem& S = *Sp;
+  if constexpr (kMode == kModeEO) {
+    tri_drain_eo(C, S, q, cnt, item0, n_tri, n_sel);
+    return;
   }
-  return sel;
+  const uint32_t lane = lane_id();
+  if (lane >= cnt) return;
+  TriHit t;
+  if (!tri_lookup(S, q[lane], item0, t)) return;
+  if constexpr (kMode == kModeCount) {  // one more triangle on each of its three edges
+    atomicAdd(&C.xcnt[t.qpos], 1u);
+    atomicAdd(&C.ie_cnt[t.k], 1u);
+    atomicAdd(C.a.tcount + t.p_yw, 1u);
+    return;
+  }
+  ++n_tri;
+  const uint32_t ly = t.y, lx = t.x, lw = t.w;
+  uint32_t t0 = ly, t1 = lx, t2 = lw;
+  sort3(t0, t1, t2);
+  const uint4 wr = tri_words(C, t0, t1, t2);
+  const uint32_t w0 = wr.x, w1 = wr.y;
+  if (!(C.thr_any && w0 <= C.thr_last)) return;
+  ++n_sel;
+  // edge e of ({t0,t1}, {t0,t2}, {t1,t2}) is the one without excl[e]
+  const uint32_t excl[3] = {t2, t1, t0};
+  const uint32_t kk = __umulhi(w1, 3u);
+  if constexpr (kMode == kModePlain) {
+    tri_mark(C.a.marks, S, kk == 0 ? t2 : (kk == 1 ? t1 : t0), lx, lw, t.k, t.qpos, t.p_yw);
+  } else if (C.op == SLIM_OP_MCTR) {
+    uint32_t n[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      n[e] = excl[e] == lw ? C.ie_cnt[t.k]
+                           : (excl[e] == ly ? C.xcnt[t.qpos] : C.a.tcount[t.p_yw]);
+    const uint32_t tmin = min(n[0], min(n[1], n[2]));
+    const uint32_t nt = (n[0] == tmin) + (n[1] == tmin) + (n[2] == tmin);
+    uint32_t pick = __umulhi(w1, nt), e = 0;
+    for (; e < 3; ++e) {
+      if (n[e] != tmin) continue;
+      if (pick == 0) break;
+      --pick;
+    }
+    tri_mark(C.a.marks, S, excl[e], lx, lw, t.k, t.qpos, t.p_yw);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if ((C.op == SLIM_OP_TR2) ? (uint32_t)e != kk : (uint32_t)e == kk)
+        tri_mark(C.a.marks, S, excl[e], lx, lw, t.k, t.qpos, t.p_yw);
+  }
 }
+
+// One window of a scan: kQuad consecutive items per lane, which sit at any
+// position (a vector load aligned to 4 bytes).
+template <int kQuad>
+struct TriWin {
+  typedef uint32_t vec __attribute__((ext_vector_type(kQuad), aligned(4)));
+  uint32_t row, rec;  // row constant of the hash; (in-edge << kItemBits) | first item
+  vec w;
+};
+template <>
+struct TriWin<1> {
+  struct vec {
+    uint32_t v;
+    __device__ uint32_t operator[](int) const { return v; }
+  };
+  uint32_t row, rec;
+  vec w;
+};
 
 // Process the in-edges bw[b0, b1) of the tile against the current hash.
-template <int kMode, int kB>
-__device__ void tri_batch(TriCtx& C, TriSmem<kB>& S, uint32_t b0, uint32_t b1, bool all_rows) {
+template <int kMode, class Smem>
+__device__ void tri_batch(TriCtx& C, Smem& S, uint32_t b0, uint32_t b1, bool all_rows) {
   constexpr bool kGeneral = kMode == kModeGeneral, kCount = kMode == kModeCount;
+  constexpr int kQuad = Smem::kQuad;
+  using Win = TriWin<kQuad>;
   const int tid = threadIdx.x;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t lane = lane_id();
   const uint32_t nin = b1 - b0;
   // ---- setup: one thread per in-edge (y,x); x is found in sorted out(y) by
   // binary search, and the items are the entries of out(y) after it
-  uint32_t cnt = 0, bmp = 0, xtag = 0;
+  uint32_t e = 0, beg = 0, len = 0, c = 0, r = 0, rs = 0, rlen = C.hlen;
   if ((uint32_t)tid < nin) {
     const uint32_t i = S.bw[b0 + tid];
     const uint64_t j = (uint64_t)C.j0 + i;
-    const uint32_t r = S.srow[i];
-    const uint32_t c = C.a.col[j];
+    r = S.srow[i];
+    c = C.a.col[j];
     const uint32_t y = C.a.rcol[j];
     const uint32_t x = C.a.rank[r];
     const uint2 yr = C.a.dag_rng[y];
     const uint32_t fs = C.a.fstart[r], fe = C.a.fstart[r + 1];
-    uint32_t e;
     bool closed = false;
     if (C.eo_later) {  // found by the first Edge-Once pass
       e = C.a.eid[j];
@@ -537,177 +600,144 @@ __device__ void tri_batch(TriCtx& C, TriSmem<kB>& S, uint32_t b0, uint32_t b1, b
     // out(x) empty: no triangle, no scan (e == yr.y only for inputs that
     // break the CSR contract: then nothing is scanned either); a closed
     // in-edge of an Edge-Once round is not scanned
-    const uint32_t beg = fe > fs && e < yr.y && !closed ? e + 1 : yr.y;
-    cnt = yr.y - beg;
-    xtag = all_rows ? (fs - C.D0) << kRowTag : 0u;
-    S.ie[tid] = make_uint4(beg, x, c, r);
-    S.ie_e[tid] = e;
-    if (kGeneral) C.ie_cnt[tid] = C.op == SLIM_OP_MCTR ? C.a.tcount[e] : 0u;
-    if (kCount) C.ie_cnt[tid] = 0u;
-    bmp = beg;
-  }
-  if ((uint32_t)tid < (kB + 31) / 32) S.ie_flag[tid] = 0;
-  if (C.ie_key && (uint32_t)tid < nin) C.ie_key[tid] = ~0ull;
-  {  // block exclusive scan of cnt into ie_pre; scan records {beg - pre, tag, next start}
-    const uint64_t incl = wave_incl_sum64(cnt);
-    if (lane == kWave - 1) S.wsum[w] = (uint32_t)incl;
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    for (int i = 0; i < kTW; ++i) {
-      if ((uint32_t)i < w) before += S.wsum[i];
-      all += S.wsum[i];
-    }
-    const uint32_t pre = before + (uint32_t)incl - cnt;
-    if ((uint32_t)tid < nin) {
-      S.ie_pre[tid] = pre;
-      S.ie_scan[tid] = make_uint4(bmp - pre, xtag, pre + cnt, 0u);
-    }
-    if (tid == 0) S.ie_pre[nin] = all;
-    __syncthreads();
-  }
-  const uint32_t W = __builtin_amdgcn_readfirstlane(S.ie_pre[nin]);
-  // ---- items: wave w takes the contiguous range [ws, we).  The current
-  // in-edge's fields stay in scalar registers; a window of 64 items crosses
-  // an in-edge boundary only now and then (a short scalar loop).
-  const uint32_t ws = (uint32_t)(((uint64_t)W * w) / kTW);
-  const uint32_t we = (uint32_t)(((uint64_t)W * (w + 1)) / kTW);
-  uint2* q = S.u.queue[w];
-  uint32_t qhead = 0, qcnt = 0;
-  uint32_t kcur = 0;
-  if (ws < we) {  // in-edge holding item ws: last k with ie_pre[k] <= ws
-    uint32_t lo = 0, hi = nin;
-    while (hi - lo > 1) {
-      const uint32_t mid = lo + ((hi - lo) >> 1);
-      if (S.ie_pre[mid] <= ws)
-        lo = mid;
-      else
-        hi = mid;
-    }
-    kcur = lo;
-  }
-  kcur = __builtin_amdgcn_readfirstlane(kcur);
-  uint32_t c_bmp, c_tag, c_nxt;  // scan begin - item base, hash tag, next in-edge start
-  auto fetch = [&](uint32_t k) {
-    const uint4 r = S.ie_scan[k];
-    c_bmp = __builtin_amdgcn_readfirstlane(r.x);
-    c_tag = __builtin_amdgcn_readfirstlane(r.y);
-    c_nxt = __builtin_amdgcn_readfirstlane(r.z);
-  };
-  fetch(kcur);
-  for (uint32_t wb = ws; wb < we; wb += kWave * kUnroll) {
-    uint32_t kk[kUnroll], xb[kUnroll], wv[kUnroll], ad[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const uint32_t base = wb + u * kWave;
-      const uint32_t t = base + lane;
-      uint32_t k = kcur, g = c_tag, p = c_bmp + t;  // p: DAG position of the item (edge {y,w})
-      const uint32_t lim = base + kWave < we ? base + kWave : we;
-      while (c_nxt < lim) {  // the next in-edge starts inside this window
-        const uint32_t bound = c_nxt;
-        ++kcur;
-        fetch(kcur);
-        const bool after = t >= bound;
-        k = after ? kcur : k;
-        p = after ? c_bmp + t : p;
-        g = after ? c_tag : g;
-      }
-      // a lane past the range gets row tag kNoRow, which no hashed key has
-      // (row tags are multiples of 16): it never hits
-      kk[u] = k;
-      xb[u] = t < we ? g : kNoRow;
-      ad[u] = t < we ? p : 0u;
-      wv[u] = C.a.dag_col[ad[u]];
-    }
-    // Probe window by window: the home bucket and the next one (four slots,
-    // read together); a key can only sit further on if an insertion went on
-    // past the second one (its kPassed bit).  The
-    // SIMDs issue vector instructions in most cycles of this loop, so the
-    // probe is written for few of them: one compare per slot key, the row
-    // tag of the first slot holding w, and the rare cases (the same w in
-    // another row of the tile, two full buckets) as divergent branches,
-    // which the exec mask skips when no lane takes them.
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const uint32_t bku = hhome(wv[u], xb[u]);
-      const uint4 e = hread(S.hb, bku);
-      const uint4 f = hread(S.hb, bku + (1u << kRowTag));  // adjacent: the spare bucket follows the last
-      const uint32_t t = wb + u * kWave + lane, wq = wv[u], g = xb[u];
-      const bool k0 = e.x == wq, k1 = e.z == wq, k2 = f.x == wq;
-      uint32_t tsel = f.w;
-      tsel = k2 ? f.y : tsel;
-      tsel = k1 ? e.w : tsel;
-      tsel = k0 ? e.y : tsel;
-      const bool kany = (k0 | k1 | k2) || f.z == wq;
-      const bool rowok = (tsel & 0xffffu) == g;
-      bool hit = kany & rowok;
-      uint32_t qpos = tsel >> 16;  // kPassed may ride along in bit 15: masked where it is used
-      bool more = !kany & ((int32_t)f.w < 0);
-      if (kany & !hit) {  // w is hashed for another row too: check all four slots
-        const bool m0 = k0 & ((e.y & 0xffffu) == g);
-        const bool m1 = k1 & ((e.w & 0xffffu) == g);
-        const bool m2 = k2 & ((f.y & 0xffffu) == g);
-        const bool m3 = (f.z == wq) & ((f.w & 0xffffu) == g);
-        hit = m0 | m1 | m2 | m3;
-        qpos = (m0 ? e.y : m1 ? e.w : m2 ? f.y : f.w) >> 16;
-        more = !hit & ((int32_t)f.w < 0);
-      }
-      uint32_t bkt = bku + (1u << kRowTag);
-      while (more) {  // an insertion went on past both buckets: keep probing (rare)
-        bkt = hnext(bkt);
-        const uint4 h = hread(S.hb, bkt);
-        const bool n0 = (h.x == wq) & ((h.y & 0xffffu) == g);
-        const bool n1 = (h.z == wq) & ((h.w & 0xffffu) == g);
-        hit = n0 | n1;
-        qpos = (n0 ? h.y : h.w) >> 16;
-        more = !(n0 | n1) & ((int32_t)h.w < 0);
-      }
-      if constexpr (kCount) {  // one more triangle on each of its three edges
-        if (hit) {
-          atomicAdd(&C.xcnt[qpos & kQposMask], 1u);
-          atomicAdd(C.a.tcount + ad[u], 1u);
-        }
-        // {y,x}: the hits of one in-edge add together (a window rarely
-        // holds more than one or two in-edges)
-        uint64_t rem = __ballot(hit);
-        while (rem) {
-          const int src = __builtin_ctzll(rem);
-          const uint32_t ks = __shfl(kk[u], src, kWave);
-          const uint64_t same = __ballot(hit && kk[u] == ks);
-          if ((int)lane == src) atomicAdd(&C.ie_cnt[ks], (uint32_t)__popcll(same));
-          rem &= ~same;
-        }
-        continue;
-      }
-      const uint64_t bal = __builtin_amdgcn_ballot_w64(hit);
-      if (bal) {
-        const uint32_t before = __builtin_amdgcn_mbcnt_hi(
-            (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        if (hit) q[(qhead + qcnt + before) % kQ] = make_uint2(t, (kk[u] << 16) | qpos);
-        qcnt += __popcll(bal);
-        if (qcnt >= (uint32_t)kWave) {
-          wave_sync();
-          C.n_sel += tri_drain<kMode, kB>(C, &S, q, qhead, kWave);
-          C.n_tri += 1;
-          qhead = (qhead + kWave) % kQ;
-          qcnt -= kWave;
-        }
-      }
+    beg = fe > fs && e < yr.y && !closed ? e + 1 : yr.y;
+    len = yr.y - beg;
+    if (all_rows) {
+      rs = fs - C.D0;
+      rlen = fe - fs;
     }
   }
-  if (qcnt) {
-    wave_sync();
-    C.n_sel += tri_drain<kMode, kB>(C, &S, q, qhead, qcnt);
-    C.n_tri += lane < qcnt ? 1 : 0;
+  const uint32_t nq = (len + kQuad - 1) / kQuad;
+  if (tid < Smem::kB) S.ie_flag[tid] = 0;
+  if (C.ie_key && tid < Smem::kB) C.ie_key[tid] = ~0ull;
+  if (tid < Smem::kM) S.mask[tid] = 0;
+  // ---- the in-edges with items, in order: index kc, first quad pre
+  const uint32_t incl = wave_incl_sum32(nq);
+  const uint64_t some = __ballot(nq != 0);
+  if (lane == kWave - 1) {
+    S.wsum[w] = incl;
+    S.wcnt[w] = __popcll(some);
   }
   __syncthreads();
-  // ---- finish: (y,x) marks, or the (y,x) counts of the counting pass
-  if (kCount) {
-    if ((uint32_t)tid < nin && C.ie_cnt[tid]) atomicAdd(C.a.tcount + S.ie_e[tid], C.ie_cnt[tid]);
-  } else if ((uint32_t)tid < nin && (S.ie_flag[tid >> 5] & (1u << (tid & 31)))) {
-    mark_set(C.a.marks, S.ie_e[tid]);
+  uint32_t pre = incl - nq, kc = __popcll(some & lanemask_lt()), W = 0, nk = 0;
+#pragma unroll
+  for (int i = 0; i < kTW; ++i) {
+    if ((uint32_t)i < w) {
+      pre += S.wsum[i];
+      kc += S.wcnt[i];
+    }
+    W += S.wsum[i];
+    nk += S.wcnt[i];
   }
-  if (C.ie_key && (uint32_t)tid < nin && C.ie_key[tid] != ~0ull)  // the batch's {y,x} bids
-    eo_bid(C.a.minkey + S.ie_e[tid], C.ie_key[tid]);
+  W = __builtin_amdgcn_readfirstlane(W);
+  nk = __builtin_amdgcn_readfirstlane(nk);
+  if (nq) {
+    S.ie_scan[kc] = make_uint2(beg - kQuad * pre, hrow(rs));
+    S.ie_tri[kc] = make_uint4(kQuad * pre + len, c - C.vb, r - C.vb, rs | (rlen << 16));
+    S.ie_pre[kc] = pre;
+    if (kGeneral) C.ie_cnt[kc] = C.op == SLIM_OP_MCTR ? C.a.tcount[e] : 0u;
+    if (kCount) C.ie_cnt[kc] = 0u;
+  }
+  // ---- items: quads [s0, s0 + n) per pass of the mask, in windows of 64
+  // (one quad per lane); wave w takes a contiguous run of windows.  The
+  // in-edge of a lane's quad is the number of mask bits below the lane, added
+  // to the count of the windows before.
+  uint2* q = S.u.queue[w];
+  uint32_t n_tri = 0, n_sel = 0;
+  for (uint32_t s0 = 0; s0 < W; s0 += Smem::kM * kWave) {
+    if (s0) {
+      __syncthreads();
+      if (tid < Smem::kM) S.mask[tid] = 0;
+      __syncthreads();
+    }
+    if (nq && pre > s0 && pre - s0 <= (uint32_t)Smem::kM * kWave)
+      atomicOr(reinterpret_cast<uint32_t*>(S.mask) + ((pre - s0 - 1) >> 5), 1u << ((pre - s0 - 1) & 31u));
+    __syncthreads();
+    const uint32_t n = W - s0 < (uint32_t)Smem::kM * kWave ? W - s0 : Smem::kM * kWave;
+    const uint32_t nwin = (n + kWave - 1) / kWave;
+    uint32_t wi = nwin * w / kTW;
+    const uint32_t we = nwin * (w + 1) / kTW;
+    if (wi >= we) continue;
+    uint32_t kcur = 0;
+    {  // in-edge of the run's first quad: last k with ie_pre[k] <= it
+      const uint32_t first = s0 + wi * kWave;
+      uint32_t lo = 0, hi = nk;
+      while (hi - lo > 1) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (S.ie_pre[mid] <= first)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      kcur = lo;
+    }
+    // loads are issued without a branch, so that the wait for one window
+    // leaves the next one's load in flight; a window past the run's end and
+    // the lanes past the last quad read the first columns (items past the
+    // end fail the look-up's end test)
+    const uint32_t item0 = kQuad * s0, last = we - 1;
+    const uint32_t lim = kQuad * (n < we * kWave ? n : we * kWave);
+    auto load = [&](uint32_t win, Win& x) {
+      const uint2 m = reinterpret_cast<const uint2*>(S.mask)[win < last ? win : last];
+      const uint32_t k = __builtin_amdgcn_mbcnt_hi(m.y, __builtin_amdgcn_mbcnt_lo(m.x, kcur));
+      kcur += __popc(m.x) + __popc(m.y);
+      const uint2 sc = S.ie_scan[k];
+      const uint32_t item = win * (kWave * kQuad) + lane * kQuad;
+      x.row = sc.y;
+      x.rec = (k << kItemBits) | item;
+      const uint32_t p = item < lim ? sc.x + item + item0 : 0u;
+      x.w = *reinterpret_cast<const typename Win::vec*>(C.a.dag_col + p);
+    };
+    uint32_t qcnt = 0;
+    auto probe = [&](const Win& x) {
+      bool cand[kQuad];
+#pragma unroll
+      for (int j = 0; j < kQuad; ++j) cand[j] = hfilter(S.filt, hkey(x.w[j], x.row));
+#pragma unroll
+      for (int j = 0; j < kQuad; ++j) {
+        const uint64_t bal = __builtin_amdgcn_ballot_w64(cand[j]);
+        if (bal == 0) continue;
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+        if (cand[j]) q[qcnt + before] = make_uint2(x.w[j], x.rec + j);
+        qcnt += __popcll(bal);
+        if (qcnt >= (uint32_t)kWave) {
+          qcnt -= kWave;
+          wave_sync();
+          tri_drain<kMode>(C, &S, q + qcnt, kWave, item0, n_tri, n_sel);
+          wave_sync();
+        }
+      }
+    };
+    Win x[kDepth];
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) load(wi + d, x[d]);
+    for (; wi < we; wi += kDepth) {
+#pragma unroll
+      for (int d = 0; d < kDepth; ++d) {
+        if (wi + d < we) probe(x[d]);
+        load(wi + d + kDepth, x[d]);
+      }
+    }
+    if (qcnt) {
+      wave_sync();
+      tri_drain<kMode>(C, &S, q, qcnt, item0, n_tri, n_sel);
+      wave_sync();
+    }
+  }
+  C.n_tri += n_tri;
+  C.n_sel += n_sel;
+  __syncthreads();
+  // ---- finish: (y,x) marks, or the (y,x) counts of the counting pass
+  if (nq) {
+    if (kCount) {
+      if (C.ie_cnt[kc]) atomicAdd(C.a.tcount + e, C.ie_cnt[kc]);
+    } else if (S.ie_flag[kc]) {
+      mark_set(C.a.marks, e);
+    }
+    if (C.ie_key && C.ie_key[kc] != ~0ull)  // the batch's {y,x} bids
+      eo_bid(C.a.minkey + e, C.ie_key[kc]);
+  }
   __syncthreads();
 }
 
@@ -715,8 +745,8 @@ __device__ void tri_batch(TriCtx& C, TriSmem<kB>& S, uint32_t b0, uint32_t b1, b
 // Edge-Once bids add the undecided triangles to the round's counter (and,
 // in the first round, T and the selected count to the graph's counters);
 // acceptance passes report nothing.
-template <int kB>
-__device__ void tri_flush_counts(TriCtx& C, TriSmem<kB>& S, uint32_t g) {
+template <class Smem>
+__device__ void tri_flush_counts(TriCtx& C, Smem& S, uint32_t g) {
   const int tid = threadIdx.x, w = tid / kWave;
   const uint64_t s0 = wave_sum64(C.n_tri), s1 = wave_sum64(C.n_sel);
   const bool first = C.a.pass < 2 || (C.a.pass == 2 && C.a.round == 1);
@@ -750,12 +780,13 @@ __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
     TriArgs a, uint32_t* tile_ctr, uint32_t cap) {
   constexpr bool kGeneral = kMode == kModeGeneral, kEO = kMode == kModeEO;
   constexpr bool kCount = kMode == kModeCount;
-  constexpr int kB = kBatchOf<kMode>;
-  using Smem = std::conditional_t<kGeneral || kCount, TriSmemGeneral<kB>,
-                                  std::conditional_t<kEO, TriSmemEO<kB>, TriSmemPlain<kB>>>;
+  constexpr int kB = kBatchOf<kMode>, kM = kMaskOf<kMode>, kQuad = kQuadOf<kMode>;
+  using Smem =
+      std::conditional_t<kGeneral || kCount, TriSmemGeneral<kB, kM, kQuad>,
+                         std::conditional_t<kEO, TriSmemEO<kB, kM, kQuad>, TriSmemPlain<kB, kM, kQuad>>>;
   static_assert(sizeof(Smem) <= kLdsPerBlock, "two blocks per CU share the LDS");
-  __shared__ Smem SS;
-  TriSmem<kB>& S = SS.s;
+  __shared__ __align__(16) Smem SS;
+  TriSmem<kB, kM, kQuad>& S = SS.s;
   TriCtx C;
   C.a = a;
   if constexpr (kGeneral || kCount) {
@@ -776,7 +807,8 @@ __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
   C.op = 0;
   C.n_tri = 0;
   C.n_sel = 0;
-  C.thr = 0;
+  C.thr_last = 0;
+  C.thr_any = false;
   C.k0 = C.k1 = C.vb = 0;
   C.eo_later = kEO && a.round > 1;
   C.eo_append = false;
@@ -806,116 +838,134 @@ __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
   const uint32_t lane = lane_id();
   const uint64_t ntiles = a.ntiles;
   uint32_t gcur = 0xffffffffu;
+  bool clean = false;  // the LDS of the tile setup and the hash is cleared
   for (;;) {
+    // ---- the next tile's index, and the clears of its setup (behind the
+    // barrier that ended the last tile's scan)
     if (tid == 0) S.bcast[0] = atomicAdd(tile_ctr, 1u);
+    if (!clean) {
+      reinterpret_cast<uint2*>(S.srow)[tid] = make_uint2(0u, 0u);
+      reinterpret_cast<uint4*>(S.u.dpos)[tid] = make_uint4(0u, 0u, 0u, 0u);
+      tri_clear_hash(S);
+      clean = true;
+    }
     __syncthreads();
-    const uint64_t t = S.bcast[0];
-    __syncthreads();
+    const uint64_t t = __builtin_amdgcn_readfirstlane(S.bcast[0]);
     if (t >= ntiles) break;
     const TileRec R = a.recs[t];
-    if (R.span == 0) continue;  // a graph without edges
     const uint32_t gop = a.gd[R.g].op;
-    // tiles of graphs that list no triangles are skipped; the counting pass
-    // visits Min-Count graphs only, the Edge-Once passes Edge-Once graphs only
-    if (!op_lists_triangles(gop)) continue;
-    if (kEO ? gop != SLIM_OP_EOTR
-            : (kCount ? gop != SLIM_OP_MCTR : gop == SLIM_OP_EOTR))
+    // graphs without edges and tiles of graphs that list no triangles are
+    // skipped; the counting pass visits Min-Count graphs only, the Edge-Once
+    // passes Edge-Once graphs only
+    bool skip = R.span == 0 || !op_lists_triangles(gop) ||
+                (kEO ? gop != SLIM_OP_EOTR : (kCount ? gop != SLIM_OP_MCTR : gop == SLIM_OP_EOTR));
+    // Edge-Once: a tile lists the same triangles in every pass, so one that
+    // found no undecided triangle in a bidding pass has none later either
+    if (kEO && C.eo_later && a.eo_live[t] + 1u < a.round) skip = true;
+    if (skip) {
+      __syncthreads();  // the index has been read
       continue;
+    }
     if (R.g != gcur) {
       // the counting pass reports no triangle or selection counts
       if (gcur != 0xffffffffu && !kCount) tri_flush_counts(C, S, gcur);
       gcur = R.g;
       const GDesc& G = a.gd[gcur];
-      C.thr = G.thr;
-      C.k0 = G.k0;
-      C.k1 = G.k1;
-      C.vb = (uint32_t)G.vb;
-      C.op = G.op;
+      C.thr_any = G.thr != 0;
+      C.thr_last = __builtin_amdgcn_readfirstlane((uint32_t)(G.thr - 1));
+      C.k0 = __builtin_amdgcn_readfirstlane(G.k0);
+      C.k1 = __builtin_amdgcn_readfirstlane(G.k1);
+      C.vb = __builtin_amdgcn_readfirstlane((uint32_t)G.vb);
+      C.op = __builtin_amdgcn_readfirstlane(G.op);
     }
-    // Edge-Once: a tile lists the same triangles in every pass, so one that
-    // found no undecided triangle in a bidding pass has none later either
-    if (kEO && C.eo_later && a.eo_live[t] + 1u < a.round) continue;
+    clean = false;
     const uint64_t sel0 = C.n_sel;
     const int64_t j0 = R.j0;
     const uint32_t span = R.span;
     C.j0 = j0;
-    tri_tile_rows(a.row_off, j0, R.lo, R.hi, S);
-    // ---- backward entries (the in-edges of the tile's rows), in CSR order
-    uint32_t fb = 0;
-    for (int k = 0; k < kChunksPerWave; ++k) {
-      const int c = w + k * kTW;
-      if (c >= kTC) break;
-      const uint32_t i = c * kWave + lane;
-      bool f = false, g = false;
-      if (i < span) {
-        const uint32_t rc = a.rcol[j0 + i], rr = a.rank[S.srow[i]];
-        f = rc < rr;
-        g = rc > rr;
-      }
-      const uint64_t m = __ballot(f);
-      const uint64_t mf = __ballot(g);
-      if (lane == 0) {
-        S.cmask[c] = m;
-        S.fwd[2 * c] = (uint32_t)mf;
-        S.fwd[2 * c + 1] = (uint32_t)(mf >> 32);
-      }
-      if (f) fb |= 1u << k;
+    // ---- rows of the tile's entries (two consecutive ones per thread): row
+    // starts into srow, then a max-scan.  Entries up to the first start
+    // belong to the row before lo.
+    uint32_t rc[2] = {0u, 0u};
+#pragma unroll
+    for (uint32_t i = 0; i < 2; ++i)
+      if (2u * tid + i < span) rc[i] = a.rcol[j0 + 2 * tid + i];
+    for (uint64_t r = R.lo + (uint64_t)tid; r < R.hi; r += kTB) {
+      const int64_t b = a.row_off[r], e = a.row_off[r + 1];
+      const int64_t s = b - j0;
+      if (e > b && s >= 0 && s < kTT) S.srow[s] = r;
     }
     __syncthreads();
-    if (w == 0) {
-      const uint32_t v = lane < kTC ? __popcll(S.cmask[lane]) : 0;
-      const uint64_t incl = wave_incl_sum64(v);
-      if (lane < kTC) S.cbase[lane] = (uint32_t)(incl - v);
-      if (lane == kWave - 1) S.bcast[1] = (uint32_t)incl;
+    uint32_t row[2];
+    {
+      const uint2 v = reinterpret_cast<const uint2*>(S.srow)[tid];
+      const uint32_t m = max(v.x, v.y);
+      const uint32_t incl = wave_incl_max(m);
+      if (lane == kWave - 1) S.wmax[w] = incl;
+      uint32_t before = __shfl_up(incl, 1, kWave);
+      if (lane == 0) before = 0;
+      __syncthreads();
+      before = max(before, R.lo > 0 ? R.lo - 1 : 0u);
+#pragma unroll
+      for (int i = 0; i < kTW; ++i)
+        if (i < w) before = max(before, S.wmax[i]);
+      row[0] = max(before, v.x);
+      row[1] = max(before, m);
+      reinterpret_cast<uint2*>(S.srow)[tid] = make_uint2(row[0], row[1]);
     }
+    // ---- backward entries (the in-edges of the tile's rows) and forward
+    // entries, each in CSR order
+    uint64_t mb[2], mf[2];
+    bool bk[2], fw[2];
+#pragma unroll
+    for (uint32_t i = 0; i < 2; ++i) {
+      bk[i] = fw[i] = false;
+      if (2u * tid + i < span) {
+        const uint32_t rr = a.rank[row[i]];
+        bk[i] = rc[i] < rr;
+        fw[i] = rc[i] > rr;
+        if (2u * tid + i == 0) S.bcast[1] = row[i];
+        if (2u * tid + i == span - 1) S.bcast[2] = row[i];
+      }
+      mb[i] = __ballot(bk[i]);
+      mf[i] = __ballot(fw[i]);
+    }
+    if (lane == 0)
+      S.wcnt[w] = (uint32_t)(__popcll(mb[0]) + __popcll(mb[1])) |
+                  ((uint32_t)(__popcll(mf[0]) + __popcll(mf[1])) << 16);
     __syncthreads();
-    for (int k = 0; k < kChunksPerWave; ++k) {
-      if (fb & (1u << k)) {
-        const int c = w + k * kTW;
-        S.bw[S.cbase[c] + __popcll(S.cmask[c] & lanemask_lt())] = (uint16_t)(c * kWave + lane);
+    uint32_t first = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < kTW; ++i) {
+      if (i < w) first += S.wcnt[i];
+      all += S.wcnt[i];
+    }
+    const uint32_t nbw = __builtin_amdgcn_readfirstlane(all & 0xffffu);
+    const uint32_t nfw = __builtin_amdgcn_readfirstlane(all >> 16);
+    const uint32_t r_lo = __builtin_amdgcn_readfirstlane(S.bcast[1]);
+    const uint32_t r_hi = __builtin_amdgcn_readfirstlane(S.bcast[2]);
+    {
+      const uint64_t lt = lanemask_lt();
+      uint32_t ib = (first & 0xffffu) + __popcll(mb[0] & lt) + __popcll(mb[1] & lt);
+      uint32_t jf = kTT - 1 - ((first >> 16) + __popcll(mf[0] & lt) + __popcll(mf[1] & lt));
+#pragma unroll
+      for (uint32_t i = 0; i < 2; ++i) {
+        if (bk[i]) S.bw[ib++] = (uint16_t)(2 * tid + i);
+        if (fw[i]) S.bw[jf--] = (uint16_t)(2 * tid + i);
       }
     }
-    const uint32_t nbw = S.bcast[1];
-    __syncthreads();
-    const uint32_t r_lo = S.srow[0], r_hi = S.srow[span - 1];
     const uint32_t D0 = a.fstart[r_lo], D1 = a.fstart[r_hi + 1];
     const bool all_rows = D1 - D0 <= C.cap;
-    if (all_rows) {
-      // ---- all rows of the tile share one hash: row start offset per position
-      const uint32_t len = D1 - D0;
-      for (uint32_t i = tid; i < len; i += kTB) S.u.dpos[i] = 0;
-      __syncthreads();
+    if (all_rows)  // ---- all rows of the tile share one hash: their starts
       for (uint64_t r = r_lo + (uint64_t)tid; r <= r_hi; r += kTB) {
         const uint32_t fs = a.fstart[r], fe = a.fstart[r + 1];
         if (fe > fs) S.u.dpos[fs - D0] = fs - D0;
       }
-      __syncthreads();
-      const uint32_t nc = (len + kWave - 1) / kWave;
-      for (uint32_t c = w; c < nc; c += kTW) {  // max-scan: chunk scans, then carry
-        const uint32_t i = c * kWave + lane;
-        const uint32_t v = wave_incl_max(i < len ? S.u.dpos[i] : 0u);
-        if (i < len) S.u.dpos[i] = v;
-        if (lane == kWave - 1) S.cbase[c] = v;
-      }
-      __syncthreads();
-      if (w == 0) {
-        const uint32_t v = lane < nc ? S.cbase[lane] : 0;
-        const uint32_t incl = wave_incl_max(v);
-        uint32_t excl = __shfl_up(incl, 1, kWave);
-        if (lane == 0) excl = 0;
-        if (lane < nc) S.cbase[lane] = excl;
-      }
-      __syncthreads();
-      for (uint32_t i = tid; i < len; i += kTB) {
-        const uint32_t v = S.u.dpos[i], cb = S.cbase[i >> 6];
-        S.u.dpos[i] = v > cb ? v : cb;
-      }
-      __syncthreads();
-    }
+    __syncthreads();
     // ---- passes: the whole tile (all_rows), or each (row, out-list chunk)
     // with its in-edges and forward entries; the hashed range is [pD0, pD0+plen)
     uint32_t r = r_lo, cur = 0, cb = 0, xe = 0, bh = 0, ea = 0, eb = 0;
-    bool row_open = false, done = false;
+    bool row_open = false, done = false, fresh = true;
     while (!done) {
       uint32_t pD0, plen, pb0, pb1, pfa, pfb;
       if (all_rows) {
@@ -973,11 +1023,17 @@ __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
         }
       }
       C.D0 = pD0;
+      if (!fresh) {  // a later pass of a tile: behind the barrier that ended the last scan
+        tri_clear_hash(S);
+        __syncthreads();
+      }
+      fresh = false;
       tri_build_hash(C, S, plen, all_rows);
-      if (!C.eo_later) tri_forward_eids(C, S, pfa, pfb, all_rows);
+      if (!C.eo_later) tri_forward_eids(C, S, nfw, pfa, pfb, all_rows);
       for (uint32_t b0 = pb0; b0 < pb1; b0 += kB)
-        tri_batch<kMode, kB>(C, S, b0, b0 + kB < pb1 ? b0 + kB : pb1, all_rows);
-      tri_flush_xbits(C, S);
+        tri_batch<kMode>(C, S, b0, b0 + kB < pb1 ? b0 + kB : pb1, all_rows);
+      if (pb0 >= pb1) __syncthreads();  // as a batch ends
+      tri_flush_xflags(C, S);
     }
     if (kEO) {  // record the round in which the tile still bid
       if (tid == 0) S.bcast[3] = 0;

@@ -509,3 +509,16 @@ def test_spectral_bad_upsilon(slim):
         with pytest.raises(slim.SlimError) as e:
             slim.spectral_sparsify(dg, bad, 1)
         assert e.value.code == slim.EINVAL
+
+
+@pytest.mark.parametrize("op", ["tr", "tr2", "mctr", "eotr"])
+@pytest.mark.parametrize("n", [129, 513, 700])
+def test_scan_passes_over_long_rows(slim, n, op):
+    """Complete graphs: the scan items of one batch of in-edges fill less than
+    one pass of the in-edge mask (n = 129), several passes of the counting
+    kernel (n = 513: up to 384 x 512 items against 16384) and of every kernel
+    (n = 700: up to 512 x 699 against 131072), with row lengths of every
+    remainder by the items per lane."""
+    g = gg.complete(n)
+    want = oracle_run(g, op, 0.5, 3) if op == "tr" else oracle_run_x(g, op, 0.5, 3)
+    assert_same(gpu_run(slim, g, op, 0.5, 3), want, f"K{n} {op}")
