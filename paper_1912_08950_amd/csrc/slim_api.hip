@@ -88,14 +88,6 @@ int check_param(int op, double p) {
   return check_p(p);
 }
 
-// 8-bit radix passes that order degrees up to maxdeg.
-int radix_passes(uint64_t maxdeg) {
-  int bits = 0;
-  while (bits < 64 && (maxdeg >> bits) != 0) ++bits;
-  int passes = (bits + 7) / 8;
-  return passes < 1 ? 1 : passes;
-}
-
 uint64_t tiles_of(uint64_t ne, uint64_t tile) {
   const uint64_t t = ceil_div(ne, tile);
   return t < 1 ? 1 : t;
@@ -114,11 +106,9 @@ SetShape single_shape(uint64_t n, uint64_t nnz, int op) {
   S.has_mc = op == SLIM_OP_MCTR;
   S.n_c = tiles_of(nnz, kTile);
   S.n_u = S.n_c;
+  S.most_c = S.n_c;
   for (int i = 0; i < 3; ++i) S.n_tri[i] = tiles_of(nnz, kTriTileMin << i);
   S.nvt = S.net = 0;
-  uint64_t maxdeg = n > 0 ? n - 1 : 0;
-  if (nnz < maxdeg) maxdeg = nnz;
-  S.passes = radix_passes(maxdeg);
   return S;
 }
 
@@ -145,41 +135,39 @@ SetLayout set_layout(const SetShape& S) {
   L.tile_cnt = c.take<uint32_t>(nt + 1);
   L.tile_base = c.take<uint64_t>(nt + 1);
   L.masks = c.take<uint64_t>(nt * (uint64_t)kChunks);
-  uint64_t st = scan_tmp_elems(nt);
+  const uint64_t st = scan_tmp_elems(nt);
   if (S.has_tr) {
     const uint64_t n = S.N, m = S.NNZ / 2;
-    const uint64_t hist = sort_hist_elems(n);
-    st = std::max(st, scan_tmp_elems(hist));
     L.recs_u = S.gathered ? c.take<TileRec>(S.n_u) : L.recs_c;
     L.recs_t = c.take<TileRec>(S.n_tri[0]);
-    L.ka = c.take<uint32_t>(n);
-    L.va = c.take<uint32_t>(n);
-    L.kb = c.take<uint32_t>(n);
-    L.vb = c.take<uint32_t>(n);
+    L.order = c.take<uint32_t>(n);
     L.rank = c.take<uint32_t>(n);
     L.rcol = c.take<uint32_t>(S.NNZ);
-    L.hist = c.take<uint32_t>(hist);
-    L.hist_scan = c.take<uint64_t>(hist + 1);
     L.fstart = c.take<uint32_t>(n + 1);
     L.dag_rng = c.take<uint2>(n);
     L.dag_col = c.take<uint32_t>(m);
     L.fence = c.take<uint32_t>(ceil_div(m, kFenceStep) + 1);
     L.eid = c.take<uint32_t>(S.NNZ);
     L.del = c.take<uint32_t>(ceil_div(m, 32) + 1);
-    L.marks = c.take<uint32_t>(ceil_div(m, 4) + 1);  // one byte per edge, filled by words
-    L.counters = c.take<uint64_t>(2 * (uint64_t)S.count);
     L.sort_lists = c.take<uint32_t>(3 * n);
-    L.sort_counts = c.take<uint32_t>(4);
-    L.tri_ctr = c.take<uint32_t>(4);
-    if (S.has_mc) L.tcount = c.take<uint32_t>(m);
     if (S.has_eo) {
       L.minkey = c.take<uint64_t>(m);
-      L.closed = c.take<uint32_t>(ceil_div(m, 32) + 1);
-      L.eo_und = c.take<uint64_t>(kEoMaxRounds + 1);
-      L.eo_live = c.take<uint32_t>(S.n_tri[0]);
       L.eo_list = c.take<uint4>(2 * 2 * kEoListPerEdge * m);  // two lists
-      L.eo_misc = c.take<uint64_t>(3);
     }
+    L.zero = c.off;
+    L.counters = c.take<uint64_t>(2 * (uint64_t)S.count);
+    L.sort_counts = c.take<uint32_t>(4);
+    L.tri_ctr = c.take<uint32_t>(4);
+    if (n > kRankSmall) L.classes = c.take<uint32_t>(2 * kDegClasses);
+    if (S.has_eo) {
+      L.eo_und = c.take<uint64_t>(kEoMaxRounds + 1);
+      L.eo_misc = c.take<uint64_t>(3);
+      L.eo_live = c.take<uint32_t>(S.n_tri[0]);
+      L.closed = c.take<uint32_t>(ceil_div(m, 32) + 1);
+    }
+    L.marks = c.take<uint32_t>(ceil_div(m, 4) + 1);  // one byte per edge, read by words
+    if (S.has_mc) L.tcount = c.take<uint32_t>(m);
+    L.zero_end = c.off;
   }
   L.scan_tmp = c.take<uint64_t>(st + 1);
   L.total = c.off;
@@ -265,12 +253,12 @@ void eo_rounds(const SetShape& S, const SetLayout& L, const Tuning& knobs, int n
   a.gcount = S.count;
   for (uint32_t r = r0; r <= r1; ++r) {
     a.round = r;
-    eo_round_start(a, s);
+    uint32_t* ctr = at<uint32_t>(ws, L.tri_ctr) + 2;
+    eo_round_start(a, ctr, s);
     eo_clear_bids(a.minkey, a.closed, S.NNZ / 2, a.eo_und, a.eo_state, a.eo_list_cnt, r, s);
     eo_list_clear(a, num_cu, s);
     a.pass = 2;
-    triangles(a, kModeEO, at<uint32_t>(ws, L.tri_ctr), num_cu, knobs.tri_blocks_per_cu,
-              knobs.tri_chunk, s);
+    triangles(a, kModeEO, ctr, num_cu, knobs.tri_blocks_per_cu, knobs.tri_chunk, s);
     eo_accept_edges(a, S.N, num_cu, s);
     eo_list_round(a, num_cu, s);
   }
@@ -278,13 +266,13 @@ void eo_rounds(const SetShape& S, const SetLayout& L, const Tuning& knobs, int n
 
 // The triangle kernel's arguments for a set whose DAG is in the workspace.
 TriArgs tri_args(const SetShape& S, const SetLayout& L, const Tuning& knobs, void* ws,
-                 const int64_t* row_off, const uint32_t* col, const uint32_t* order) {
+                 const int64_t* row_off, const uint32_t* col) {
   TriArgs a{};
   a.row_off = row_off;
   a.col = col;
   a.rank = at<uint32_t>(ws, L.rank);
   a.rcol = at<uint32_t>(ws, L.rcol);
-  a.order = order;
+  a.order = at<uint32_t>(ws, L.order);
   a.dag_rng = at<uint2>(ws, L.dag_rng);
   a.fstart = at<uint32_t>(ws, L.fstart);
   a.dag_col = at<uint32_t>(ws, L.dag_col);
@@ -298,17 +286,28 @@ TriArgs tri_args(const SetShape& S, const SetLayout& L, const Tuning& knobs, voi
   a.tcount = S.has_mc ? at<uint32_t>(ws, L.tcount) : nullptr;
   return a;
 }
-// Enqueues every phase of a set whose header (descriptors and tile
-// prefixes) is already in the workspace.  `row_off`/`col` are the caller's
-// CSR for a single graph; a gathered set builds its union in the workspace.
+// Output CSRs and counters of a set from the marks.
+void finish_set(const SetShape& S, const SetLayout& L, void* ws, const int64_t* row_off,
+                const uint32_t* col, bool tr, hipStream_t s) {
+  uint32_t* del = tr ? at<uint32_t>(ws, L.del) : nullptr;
+  if (tr) pack_marks(at<uint8_t>(ws, L.marks), del, S.NNZ / 2, s);
+  compact_out(row_off, col, tr ? at<uint32_t>(ws, L.eid) : nullptr, del, S.NNZ / 2,
+              at<GDesc>(ws, L.gd), S.count, at<uint64_t>(ws, L.t0c), at<TileRec>(ws, L.recs_c),
+              S.n_c, S.most_c, at<uint32_t>(ws, L.tile_cnt), at<uint64_t>(ws, L.masks),
+              at<uint64_t>(ws, L.tile_base), at<uint64_t>(ws, L.scan_tmp),
+              tr ? at<uint64_t>(ws, L.counters) : nullptr, s);
+}
+
+// Enqueues every phase of a set.  The header (descriptors and tile prefixes)
+// of a one-graph set comes in `hdr` and is written by the first launch; that
+// of a gathered set is already in the workspace.  `row_off`/`col` are the
+// caller's CSR for a single graph; a gathered set builds its union in the
+// workspace.
 void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num_cu, void* ws,
-             const int64_t* row_off, const uint32_t* col, hipStream_t s, bool profile) {
+             const int64_t* row_off, const uint32_t* col, const void* hdr, uint32_t hdr_bytes,
+             hipStream_t s, bool profile) {
   const GDesc* gd = at<GDesc>(ws, L.gd);
   const uint64_t* t0c = at<uint64_t>(ws, L.t0c);
-  uint32_t* tile_cnt = at<uint32_t>(ws, L.tile_cnt);
-  uint64_t* tile_base = at<uint64_t>(ws, L.tile_base);
-  uint64_t* scan_tmp = at<uint64_t>(ws, L.scan_tmp);
-  TileRec* recs_c = at<TileRec>(ws, L.recs_c);
   const bool tr = S.has_tr && S.NNZ > 0;
   prof_begin(profile, tr ? "rank" : "sample", s);
   if (S.gathered) {
@@ -319,92 +318,66 @@ void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num
     row_off = urow;
     col = ucol;
   }
-  tile_recs(row_off, gd, t0c, S.count, S.n_c, kTile, recs_c, s);
-  uint32_t* eid = nullptr;
-  uint32_t* del = nullptr;
-  uint64_t* counters = nullptr;
+  const uint64_t n_t = S.n_t(knobs.tri_tile);
+  SetupArgs u{};
+  if (hdr) {
+    std::memcpy(u.hdr, hdr, hdr_bytes);
+    u.hdr_words = hdr_bytes / 4;
+    u.hdr_dst = at<uint32_t>(ws, L.gd);
+  }
+  u.row_off = row_off;
+  u.n = S.N;
+  u.nnz = S.NNZ;
+  u.gd = gd;
+  const uint32_t graphs = S.gathered ? S.count : 0;  // 0: one graph, the whole CSR
+  u.rec[0] = RecJob{t0c, graphs, S.n_c, (uint64_t)kTile, at<TileRec>(ws, L.recs_c)};
   if (tr) {
-    uint32_t* rank = at<uint32_t>(ws, L.rank);
-    uint32_t* order = nullptr;
-    degree_rank(row_off, S.N, S.passes, at<uint32_t>(ws, L.ka), at<uint32_t>(ws, L.va),
-                at<uint32_t>(ws, L.kb), at<uint32_t>(ws, L.vb), at<uint32_t>(ws, L.hist),
-                at<uint64_t>(ws, L.hist_scan), scan_tmp, &order, rank, s);
+    u.rec[1] = RecJob{at<uint64_t>(ws, L.t0t), graphs, n_t, (uint64_t)knobs.tri_tile,
+                      at<TileRec>(ws, L.recs_t)};
+    if (S.gathered) u.rec[2] = RecJob{nullptr, 0, S.n_u, (uint64_t)kTile, at<TileRec>(ws, L.recs_u)};
+    u.order = at<uint32_t>(ws, L.order);
+    u.rank = at<uint32_t>(ws, L.rank);
+    u.fill[0] = FillJob{at<uint4>(ws, L.zero), (L.zero_end - L.zero) / sizeof(uint4), 0u};
+  }
+  setup(u, s);
+  if (tr) {
+    degree_rank(row_off, S.N, at<uint32_t>(ws, L.classes), u.order, u.rank, s);
     prof_end(profile, s);
     prof_begin(profile, "orient", s);
     const GDesc* gu = gd + S.count;
     const uint64_t* t0u = S.gathered ? at<uint64_t>(ws, L.t0u) : t0c;
-    TileRec* recs_u = at<TileRec>(ws, L.recs_u);
-    if (S.gathered) tile_recs(row_off, gu, t0u, 1, S.n_u, kTile, recs_u, s);
     uint32_t* fstart = at<uint32_t>(ws, L.fstart);
     uint32_t* dag_col = at<uint32_t>(ws, L.dag_col);
     uint2* dag_rng = at<uint2>(ws, L.dag_rng);
-    uint32_t* rcol = at<uint32_t>(ws, L.rcol);
-    orient(row_off, col, rank, rcol, gu, t0u, recs_u, S.n_u, tile_cnt, at<uint64_t>(ws, L.masks),
-           tile_base, scan_tmp, s);
-    dag_ranges(order, fstart, S.N, dag_rng, s);
+    orient(row_off, col, u.rank, at<uint32_t>(ws, L.rcol), gu, t0u, at<TileRec>(ws, L.recs_u),
+           S.n_u, at<uint32_t>(ws, L.tile_cnt), at<uint64_t>(ws, L.masks),
+           at<uint64_t>(ws, L.tile_base), at<uint64_t>(ws, L.scan_tmp), s);
+    dag_ranges(u.order, fstart, S.N, dag_rng, s);
     sort_rows(dag_rng, S.N, dag_col, at<uint32_t>(ws, L.sort_lists),
               at<uint32_t>(ws, L.sort_counts), num_cu, s);
-    uint32_t* fence = at<uint32_t>(ws, L.fence);
-    fence_samples(dag_col, S.NNZ / 2, fence, s);
-    eid = at<uint32_t>(ws, L.eid);
-    del = at<uint32_t>(ws, L.del);
-    counters = at<uint64_t>(ws, L.counters);
-    TileRec* recs_t = at<TileRec>(ws, L.recs_t);
-    const uint64_t n_t = S.n_t(knobs.tri_tile);
-    tile_recs(row_off, gd, at<uint64_t>(ws, L.t0t), S.count, n_t, (uint64_t)knobs.tri_tile,
-              recs_t, s);
-    uint8_t* marks = at<uint8_t>(ws, L.marks);
-    fill_u32(reinterpret_cast<uint32_t*>(marks), ceil_div(S.NNZ / 2, 4) + 1, 0, s);
-    fill_u32(reinterpret_cast<uint32_t*>(counters), 4 * (uint64_t)S.count, 0, s);
+    fence_samples(dag_col, S.NNZ / 2, at<uint32_t>(ws, L.fence), s);
     prof_end(profile, s);
     prof_begin(profile, "triangles", s);
-    TriArgs a{};
-    a.row_off = row_off;
-    a.col = col;
-    a.rank = rank;
-    a.rcol = rcol;
-    a.order = order;
-    a.dag_rng = dag_rng;
-    a.fstart = fstart;
-    a.dag_col = dag_col;
-    a.fence = fence;
-    a.eid = eid;
-    a.marks = marks;
-    a.counters = counters;
-    a.gd = gd;
-    a.recs = recs_t;
-    a.ntiles = n_t;
-    a.tcount = S.has_mc ? at<uint32_t>(ws, L.tcount) : nullptr;
-    a.round = 0;
+    TriArgs a = tri_args(S, L, knobs, ws, row_off, col);
+    uint32_t* ctr = at<uint32_t>(ws, L.tri_ctr);
     if (S.has_mc) {  // Min-Count: per-edge triangle counts first
-      fill_u32(a.tcount, S.NNZ / 2, 0, s);
       a.pass = 0;
-      triangles(a, kModeCount, at<uint32_t>(ws, L.tri_ctr), num_cu, knobs.tri_blocks_per_cu,
-                knobs.tri_chunk, s);
+      triangles(a, kModeCount, ctr, num_cu, knobs.tri_blocks_per_cu, knobs.tri_chunk, s);
     }
     if (S.has_list) {
       a.pass = 1;
-      triangles(a, S.general ? kModeGeneral : kModePlain, at<uint32_t>(ws, L.tri_ctr), num_cu,
+      triangles(a, S.general ? kModeGeneral : kModePlain, ctr + 1, num_cu,
                 knobs.tri_blocks_per_cu, knobs.tri_chunk, s);
     }
     prof_end(profile, s);
     if (S.has_eo) {
       prof_begin(profile, "eo_rounds", s);
-      fill_u32(at<uint32_t>(ws, L.closed), ceil_div(S.NNZ / 2, 32) + 1, 0, s);
-      fill_u32(reinterpret_cast<uint32_t*>(at<uint64_t>(ws, L.eo_und)), 2 * (kEoMaxRounds + 1),
-               0, s);
-      fill_u32(at<uint32_t>(ws, L.eo_live), S.n_t(knobs.tri_tile), 0, s);
-      fill_u32(reinterpret_cast<uint32_t*>(at<uint64_t>(ws, L.eo_misc)), 6, 0, s);
       eo_rounds(S, L, knobs, num_cu, ws, a, 1, (uint32_t)knobs.eo_rounds, s);
       prof_end(profile, s);
     }
     prof_begin(profile, "compact", s);
-    pack_marks(marks, del, S.NNZ / 2, s);
   }
-  compact_out(row_off, col, eid, del, S.NNZ / 2, gd, t0c, recs_c, S.n_c, tile_cnt,
-              at<uint64_t>(ws, L.masks), tile_base,
-              scan_tmp, s);
-  write_stats(gd, S.count, t0c, counters, tile_base, s);
+  finish_set(S, L, ws, row_off, col, tr, s);
   prof_end(profile, s);
 }
 
@@ -428,23 +401,13 @@ int eo_finish(const SetShape& S, const SetLayout& L, const Tuning& knobs, int nu
     if (u == 0) break;
     if (last + step > kEoMaxRounds)
       return fail(SLIM_EDEVICE, "Edge-Once: undecided triangles after %u rounds", last);
-    const uint32_t* order = at<uint32_t>(ws, S.passes % 2 ? L.vb : L.va);
-    eo_rounds(S, L, knobs, num_cu, ws, tri_args(S, L, knobs, ws, row_off, col, order), last + 1,
+    eo_rounds(S, L, knobs, num_cu, ws, tri_args(S, L, knobs, ws, row_off, col), last + 1,
               last + step, s);
     last += step;
     more = true;
   }
-  if (more) {  // the first compaction saw the marks of the first rounds only
-    const GDesc* gd = at<GDesc>(ws, L.gd);
-    const uint64_t* t0c = at<uint64_t>(ws, L.t0c);
-    uint64_t* tile_base = at<uint64_t>(ws, L.tile_base);
-    pack_marks(at<uint8_t>(ws, L.marks), at<uint32_t>(ws, L.del), S.NNZ / 2, s);
-    compact_out(row_off, col, at<uint32_t>(ws, L.eid), at<uint32_t>(ws, L.del), S.NNZ / 2, gd,
-                t0c, at<TileRec>(ws, L.recs_c), S.n_c, at<uint32_t>(ws, L.tile_cnt),
-                at<uint64_t>(ws, L.masks), tile_base,
-                at<uint64_t>(ws, L.scan_tmp), s);
-    write_stats(gd, S.count, t0c, at<uint64_t>(ws, L.counters), tile_base, s);
-  }
+  if (more)  // the first compaction saw the marks of the first rounds only
+    finish_set(S, L, ws, row_off, col, true, s);
   return SLIM_OK;
 }
 
@@ -529,7 +492,7 @@ struct SingleHdr {
   uint64_t t0t[2];
   uint64_t t0u[2];
 };
-static_assert(sizeof(SingleHdr) <= 512, "one put_bytes launch");
+static_assert(sizeof(SingleHdr) <= sizeof(SetupArgs::hdr), "one setup launch");
 static_assert(sizeof(GDesc) == 120, "descriptor size");
 
 int single_op(int op, const slim_graph* g, double p, uint64_t seed, void* ws, uint64_t ws_bytes,
@@ -592,8 +555,7 @@ int single_op(int op, const slim_graph* g, double p, uint64_t seed, void* ws, ui
   if (L.t0c != offsetof(SingleHdr, t0c) || L.t0t != offsetof(SingleHdr, t0t) ||
       L.t0u != offsetof(SingleHdr, t0u))
     return fail(SLIM_EDEVICE, "internal: set header layout");
-  put_bytes(at<char>(ws, L.gd), &h, sizeof(h), s);
-  run_set(S, L, knobs, g->num_cu, ws, g->row_off, g->col, s, profile);
+  run_set(S, L, knobs, g->num_cu, ws, g->row_off, g->col, &h, sizeof(h), s, profile);
   if (int rc = hip_check(what)) return rc;
   if (int rc = eo_finish(S, L, knobs, g->num_cu, ws, g->row_off, g->col, s)) return rc;
   return hip_check(what);
@@ -665,15 +627,13 @@ int slim_load_csr(const int64_t* d_row_off, const uint32_t* d_col, uint64_t n, u
   if (flags & SLIM_VALIDATE) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t ntiles = tiles_of(nnz, kTile);
-    // err word, then a one-graph set header and its tile records
-    const uint64_t hdr = 256, recs_off = 2 * hdr;
+    // err word, then the tile records of the one graph
+    const uint64_t recs_off = 256;
     const uint64_t bytes = recs_off + sizeof(TileRec) * ntiles;
     char* buf = nullptr;
     if (hipMalloc(&buf, bytes) != hipSuccess)
       return fail(SLIM_EDEVICE, "validation buffer allocation failed");
     uint32_t* err = reinterpret_cast<uint32_t*>(buf);
-    GDesc* gd = reinterpret_cast<GDesc*>(buf + hdr);
-    uint64_t* t0 = reinterpret_cast<uint64_t*>(buf + hdr + sizeof(GDesc));
     TileRec* recs = reinterpret_cast<TileRec*>(buf + recs_off);
     uint32_t h_err = 0;
     fill_u32(err, 1, 0, s);
@@ -681,15 +641,12 @@ int slim_load_csr(const int64_t* d_row_off, const uint32_t* d_col, uint64_t n, u
     hipError_t e = hipMemcpyAsync(&h_err, err, sizeof(h_err), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess && h_err == 0 && nnz) {
-      struct {
-        GDesc d;
-        uint64_t t0[2];
-      } h{};
-      h.d.nv = n;
-      h.d.ne = nnz;
-      h.t0[1] = ntiles;
-      put_bytes(gd, &h, sizeof(h), s);
-      tile_recs(d_row_off, gd, t0, 1, ntiles, kTile, recs, s);
+      SetupArgs u{};
+      u.row_off = d_row_off;
+      u.n = n;
+      u.nnz = nnz;
+      u.rec[0] = RecJob{nullptr, 0, ntiles, (uint64_t)kTile, recs};
+      setup(u, s);
       validate_entries(d_row_off, d_col, n, recs, ntiles, err, s);
       e = hipMemcpyAsync(&h_err, err, sizeof(h_err), hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);

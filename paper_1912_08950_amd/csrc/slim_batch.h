@@ -33,7 +33,7 @@ struct SetShape {
   uint64_t n_u = 0;         // union tiles of kTile entries (orientation)
   uint64_t n_tri[3] = {0, 0, 0};  // graph-aligned triangle tiles of 256, 512, 1024 entries
   uint64_t nvt = 0, net = 0;      // gather chunks: vertex and entry
-  int passes = 1;                 // radix passes of the degree sort
+  uint64_t most_c = 0;            // compaction tiles of the largest graph
   uint64_t n_t(int tile) const { return n_tri[tile <= 256 ? 0 : tile <= 512 ? 1 : 2]; }
 };
 
@@ -43,10 +43,12 @@ struct SetLayout {
   uint64_t urow, ucol;
   uint64_t recs_c, recs_u, recs_t;
   uint64_t tile_cnt, tile_base, scan_tmp, masks;
-  uint64_t ka, va, kb, vb, rank, rcol, hist, hist_scan;
-  uint64_t fstart, dag_rng, dag_col, fence, eid, del, marks, counters;
-  uint64_t sort_lists, sort_counts, tri_ctr, tcount;
-  uint64_t minkey, closed, eo_und, eo_live, eo_list, eo_misc;
+  uint64_t order, rank, rcol;
+  uint64_t fstart, dag_rng, dag_col, fence, eid, del, sort_lists;
+  uint64_t minkey, eo_list;
+  // cleared by the setup: [zero, zero_end)
+  uint64_t zero, counters, sort_counts, tri_ctr, classes, eo_und, eo_misc, eo_live, closed, marks,
+      tcount, zero_end;
   uint64_t total;
 };
 
@@ -59,12 +61,14 @@ int check_p(double p);
 // p of an operation: a probability in [0,1], or upsilon >= 0 for spectral
 // sparsification.
 int check_param(int op, double p);
-int radix_passes(uint64_t maxdeg);
 uint64_t tiles_of(uint64_t ne, uint64_t tile);
 SetLayout set_layout(const SetShape& S);
 GDesc union_desc(const SetShape& S, const SetLayout& L, void* ws);
+// hdr: header of a one-graph set (hdr_words words, written by the first
+// launch), or NULL where it is in the workspace already.
 void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num_cu, void* ws,
-             const int64_t* row_off, const uint32_t* col, hipStream_t s, bool profile);
+             const int64_t* row_off, const uint32_t* col, const void* hdr, uint32_t hdr_bytes,
+             hipStream_t s, bool profile);
 // Sets with Edge-Once graphs: after run_set (or the replay of its capture)
 // on stream s, waits for s, runs further rounds while the last one still
 // found undecided triangles and then compacts again.  SLIM_OK at once for

@@ -2,6 +2,7 @@
 // the set header (per-graph descriptors and tile prefixes), a run refreshes
 // it in the workspace with one copy when it changed, and the launch sequence
 // of the set is captured once into a HIP graph and replayed.
+#include <algorithm>
 #include <chrono>
 #include <cstdio>
 #include <cstring>
@@ -27,7 +28,7 @@ int plan_set(const std::vector<GDesc>& graphs, SetPlan& P) {
   S = SetShape{};
   S.count = count;
   S.gathered = true;
-  uint64_t N = 0, NNZ = 0, maxdeg = 0;
+  uint64_t N = 0, NNZ = 0;
   for (uint32_t g = 0; g < count; ++g) {
     GDesc d = graphs[g];
     d.vb = N;
@@ -39,6 +40,7 @@ int plan_set(const std::vector<GDesc>& graphs, SetPlan& P) {
     P.vt0[g] = S.nvt;
     P.et0[g] = S.net;
     S.n_c += tiles_of(d.ne, kTile);
+    S.most_c = std::max(S.most_c, tiles_of(d.ne, kTile));
     for (int i = 0; i < 3; ++i) S.n_tri[i] += tiles_of(d.ne, kTriTileMin << i);
     S.nvt += (d.nv + kTile - 1) / kTile;
     S.net += (d.ne + kTile - 1) / kTile;
@@ -49,9 +51,6 @@ int plan_set(const std::vector<GDesc>& graphs, SetPlan& P) {
       S.has_eo = true;
     else if (op_lists_triangles(d.op))
       S.has_list = true;
-    uint64_t md = d.nv > 0 ? d.nv - 1 : 0;
-    if (d.ne < md) md = d.ne;
-    if (md > maxdeg) maxdeg = md;
     N += d.nv;
     NNZ += d.ne;
   }
@@ -64,7 +63,6 @@ int plan_set(const std::vector<GDesc>& graphs, SetPlan& P) {
   S.N = N;
   S.NNZ = NNZ;
   S.n_u = tiles_of(NNZ, kTile);
-  S.passes = radix_passes(maxdeg);
   return SLIM_OK;
 }
 
@@ -192,7 +190,7 @@ int run(slim_batch* b, void* ws, uint64_t ws_bytes, const slim_out_t* outs, hipS
   };
   if (!b->use_graph) {  // direct launches: phases are timed when profiling is on
     prof_reset();
-    run_set(b->plan.shape, b->layout, b->knobs, b->num_cu, ws, nullptr, nullptr, s, true);
+    run_set(b->plan.shape, b->layout, b->knobs, b->num_cu, ws, nullptr, nullptr, nullptr, 0, s, true);
     if (int rc = hip_check("slim_batch_run")) return rc;
     if (int rc = eo_finish(b->plan.shape, b->layout, b->knobs, b->num_cu, ws, nullptr, nullptr, s))
       return rc;
@@ -202,7 +200,8 @@ int run(slim_batch* b, void* ws, uint64_t ws_bytes, const slim_out_t* outs, hipS
     drop_graph(b);
     if (hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeRelaxed) != hipSuccess)
       return fail(SLIM_EDEVICE, "hipStreamBeginCapture failed");
-    run_set(b->plan.shape, b->layout, b->knobs, b->num_cu, ws, nullptr, nullptr, b->cap_stream, false);
+    run_set(b->plan.shape, b->layout, b->knobs, b->num_cu, ws, nullptr, nullptr, nullptr, 0,
+            b->cap_stream, false);
     hipGraph_t gr = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap_stream, &gr);
     if (e != hipSuccess || !gr) {

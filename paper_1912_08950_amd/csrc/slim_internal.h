@@ -55,18 +55,46 @@ uint64_t scan_tmp_elems(uint64_t len);
 template <typename TI>
 void scan_excl(const TI* in, uint64_t len, uint64_t* out, uint64_t* tmp, hipStream_t s);
 
-uint64_t sort_hist_elems(uint64_t n);
-void degree_rank(const int64_t* row_off, uint64_t n, int passes, uint32_t* ka, uint32_t* va,
-                 uint32_t* kb, uint32_t* vb, uint32_t* hist, uint64_t* hist_scan,
-                 uint64_t* scan_tmp, uint32_t** order_out, uint32_t* rank, hipStream_t s);
+// Ranks of the vertices by degree class, in rank[] and (inverse) order[];
+// classes: 2 * kDegClasses cleared words (unused up to kRankSmall vertices,
+// which setup() ranks).
+constexpr uint32_t kDegClasses = 2432;
+constexpr uint64_t kRankSmall = 4096;
+void degree_rank(const int64_t* row_off, uint64_t n, uint32_t* classes, uint32_t* order,
+                 uint32_t* rank, hipStream_t s);
 
 // Copies up to 512 bytes of host data (descriptors) to device memory by a
 // kernel launch: no host-to-device copy, so it can sit in a captured graph.
 void put_bytes(void* dst, const void* src, uint32_t bytes, hipStream_t s);
-// Tile records of a set with `tile` entries per tile; tile0[g] is the first
-// tile of graph g (tile0[count] = ntiles; every graph has at least one tile).
-void tile_recs(const int64_t* row_off, const GDesc* gd, const uint64_t* tile0, uint32_t count,
-               uint64_t ntiles, uint64_t tile, TileRec* recs, hipStream_t s);
+// The first launch of a set: what depends on nothing but the CSR.
+struct RecJob {  // tile records with `tile` entries per tile
+  const uint64_t* tile0;  // tile0[g]: first tile of graph g (tile0[count] = ntiles;
+  uint32_t count;         //   every graph has at least one tile); count 0: one graph
+  uint64_t ntiles, tile;  //   that is the whole CSR
+  TileRec* recs;
+};
+struct FillJob {  // p[0 .. quads) = {v, v, v, v}
+  uint4* p;
+  uint64_t quads;
+  uint32_t v;
+};
+constexpr int kMaxRecs = 3, kMaxFills = 1;
+constexpr int kJobHeader = 0, kJobRank = 1, kJobRecs = 2, kJobFill = kJobRecs + kMaxRecs;
+constexpr int kSetupJobs = kJobFill + kMaxFills;
+struct SetupArgs {
+  uint32_t hdr[96];  // header of a one-graph set, hdr_words long (0: none)
+  uint32_t hdr_words;
+  uint32_t* hdr_dst;
+  const int64_t* row_off;
+  uint64_t n, nnz;
+  const GDesc* gd;
+  uint32_t* order;  // NULL: no ranks
+  uint32_t* rank;
+  RecJob rec[kMaxRecs];
+  FillJob fill[kMaxFills];
+  uint32_t nb[kSetupJobs];  // blocks per job, set by setup()
+};
+void setup(SetupArgs& a, hipStream_t s);
 // Gathers the graphs of a set into the union CSR (union ids in ucol).
 // vtile0 / etile0: per-graph prefixes of kTile-sized vertex / entry chunks.
 void gather(const GDesc* gd, uint32_t count, const uint64_t* vtile0, const uint64_t* etile0,
@@ -88,14 +116,14 @@ void dag_ranges(const uint32_t* order, const uint32_t* fstart, uint64_t n, uint2
 // Packs the per-edge deletion bytes into the bitmap the compaction reads
 // (32 bytes -> one word).
 void pack_marks(const uint8_t* marks, uint32_t* del, uint64_t m, hipStream_t s);
+// The last tile of a graph writes its counters (2 per graph in `counters`, or
+// NULL) to its stats.  most_tiles: tiles of the largest graph.
+constexpr uint64_t kSelfScan = 8192;
 void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* eid,
-                 const uint32_t* del, uint64_t m, const GDesc* gd, const uint64_t* tile0,
-                 const TileRec* recs, uint64_t ntiles, uint32_t* tile_cnt, uint64_t* masks,
-                 uint64_t* tile_base, uint64_t* scan_tmp, hipStream_t s);
-// Per-graph stats from the triangle counters (2 per graph, may be NULL) and
-// the compaction's tile scan.
-void write_stats(const GDesc* gd, uint32_t count, const uint64_t* tile0,
-                 const uint64_t* counters, const uint64_t* tile_base, hipStream_t s);
+                 const uint32_t* del, uint64_t m, const GDesc* gd, uint32_t count,
+                 const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
+                 uint32_t* tile_cnt, uint64_t* masks, uint64_t* tile_base, uint64_t* scan_tmp,
+                 const uint64_t* counters, hipStream_t s);
 void validate_offsets(const int64_t* row_off, uint64_t n, uint64_t nnz, uint32_t* err,
                       hipStream_t s);
 void validate_entries(const int64_t* row_off, const uint32_t* col, uint64_t n,
@@ -151,6 +179,7 @@ uint64_t tri_tile_max();
 // counting (the Min-Count counting pass: per-edge triangle counts only, no
 // selection).
 constexpr int kModePlain = 0, kModeGeneral = 1, kModeEO = 2, kModeCount = 3;
+// tile_ctr: a cleared word of the launch's own.
 void triangles(const TriArgs& a, int mode, uint32_t* tile_ctr, int num_cu,
                int blocks_per_cu, int chunk, hipStream_t s);
 
@@ -192,7 +221,7 @@ void eo_clear_bids(uint64_t* minkey, uint32_t* closed, uint64_t m, const uint64_
 void eo_accept_edges(const TriArgs& a, uint64_t n, int num_cu, hipStream_t s);
 // Start of round a.round: a list that the previous round started but
 // overflowed is dropped (the round accepted by the edge-parallel kernel).
-void eo_round_start(const TriArgs& a, hipStream_t s);
+void eo_round_start(const TriArgs& a, uint32_t* tile_ctr, hipStream_t s);
 // Clears the bids of the previous round through its list records, when the
 // round runs on the lists and they are few (k_eo_clear_bids sweeps otherwise).
 void eo_list_clear(const TriArgs& a, int num_cu, hipStream_t s);

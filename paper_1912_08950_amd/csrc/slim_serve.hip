@@ -333,7 +333,7 @@ int run_batch(slim_server* S, Worker& W, const std::vector<Job*>& batch) {
       rc = fail(SLIM_EDEVICE, "serve: header upload failed");
     } else {
       (void)hipGetLastError();
-      run_set(P.shape, L, S->knobs, S->num_cu, ws, nullptr, nullptr, s, false);
+      run_set(P.shape, L, S->knobs, S->num_cu, ws, nullptr, nullptr, nullptr, 0, s, false);
       hipError_t e = hipGetLastError();
       if (e == hipSuccess && eo_finish(P.shape, L, S->knobs, S->num_cu, ws, nullptr, nullptr, s))
         e = hipErrorUnknown;

@@ -230,7 +230,6 @@ void fence_samples(const uint32_t* dag_col, uint64_t m, uint32_t* fence, hipStre
 
 void sort_rows(const uint2* dag_rng, uint64_t n, uint32_t* dag_col, uint32_t* lists,
                uint32_t* counts, int num_cu, hipStream_t s) {
-  fill_u32(counts, 4, 0, s);
   uint32_t* wave_list = lists;
   uint32_t* block_list = lists + n;
   uint32_t* huge_list = lists + 2 * n;

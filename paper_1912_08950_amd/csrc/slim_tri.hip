@@ -1073,7 +1073,8 @@ __device__ __forceinline__ bool eo_listed_round(const TriArgs& a, bool accept) {
          (listed < a.round || (accept && listed == a.round && !eo_list_overflow(a)));
 }
 
-__global__ void k_eo_round_start(TriArgs a) {
+__global__ void k_eo_round_start(TriArgs a, uint32_t* tile_ctr) {
+  *tile_ctr = 0;
   const uint32_t listed = a.eo_state[0];
   if (listed != 0 && listed + 1 == a.round && eo_list_overflow(a)) {
     a.eo_state[0] = 0;
@@ -1277,8 +1278,8 @@ void eo_accept_edges(const TriArgs& a, uint64_t n, int num_cu, hipStream_t s) {
   hipLaunchKernelGGL(k_eo_accept_edges, dim3(blocks), dim3(kListBlock), 0, s, a, n);
 }
 
-void eo_round_start(const TriArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_eo_round_start, dim3(1), dim3(1), 0, s, a);
+void eo_round_start(const TriArgs& a, uint32_t* tile_ctr, hipStream_t s) {
+  hipLaunchKernelGGL(k_eo_round_start, dim3(1), dim3(1), 0, s, a, tile_ctr);
 }
 
 void eo_list_clear(const TriArgs& a, int num_cu, hipStream_t s) {
@@ -1299,7 +1300,6 @@ void triangles(const TriArgs& a, int mode, uint32_t* tile_ctr, int num_cu,
   uint64_t blocks = (uint64_t)num_cu * blocks_per_cu;
   if (blocks > a.ntiles) blocks = a.ntiles;
   if (blocks < 1) blocks = 1;
-  fill_u32(tile_ctr, 1, 0, s);
   uint32_t cap = (uint32_t)chunk;
   if (cap > (uint32_t)kHashCap) cap = kHashCap;
   if (mode == kModeGeneral)

@@ -522,3 +522,36 @@ def test_scan_passes_over_long_rows(slim, n, op):
     g = gg.complete(n)
     want = oracle_run(g, op, 0.5, 3) if op == "tr" else oracle_run_x(g, op, 0.5, 3)
     assert_same(gpu_run(slim, g, op, 0.5, 3), want, f"K{n} {op}")
+
+
+def padded(g, before, after):
+    """g with `before` isolated vertices ahead of it and `after` behind it."""
+    ro = np.concatenate([np.zeros(before, np.int64), g.row_off,
+                         np.full(after, g.row_off[-1], np.int64)])
+    return gg.CSR(ro, (g.col + np.uint32(before)).astype(np.uint32), f"{g.name}+{before}+{after}")
+
+
+@pytest.mark.parametrize("op", ["es", "spectral", "tr"])
+@pytest.mark.parametrize("entries", [2, 6, 254, 256, 258, 1022, 1024, 1026, 4094, 4096, 4098, 8194,
+                                     12290])
+def test_compaction_boundaries(slim, entries, op):
+    """CSRs whose entries end at or beside the edges of a lane's vector, a
+    wave's group, a wave's span and a tile (4, 256, 1024 and 4096 entries), as
+    one long row and as rows of two, with runs of empty rows around them; the
+    vertex counts lie on both sides of the one-block ranking (4096) and the
+    hub degrees on both sides of the exact degree classes (1024)."""
+    m = entries // 2
+    graphs = [padded(gg.star(m + 1), 0, 0), padded(gg.star(m + 1), 300, 5000)]
+    if m >= 3:
+        graphs.append(padded(gg.cycle(m), 4500, 1))
+    for g in graphs:
+        assert g.nnz == entries
+        if op == "spectral":
+            dg = slim.Graph.from_csr(g)
+            bufs = slim.spectral_sparsify(dg, 1.3, 5)
+            ro, col, st = slim.result_numpy(bufs)
+            oro, ocol, ow, ost = O.spectral_sparsify(g, 1.3, 5)
+            assert np.array_equal(ro, oro) and np.array_equal(col, ocol), g.name
+            assert np.array_equal(slim.weights_numpy(bufs), ow), g.name
+        else:
+            assert_same(gpu_run(slim, g, op, 0.5, 5), oracle_run(g, op, 0.5, 5), g.name)
