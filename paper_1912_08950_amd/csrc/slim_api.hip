@@ -347,15 +347,12 @@ void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num
     const GDesc* gu = gd + S.count;
     const uint64_t* t0u = S.gathered ? at<uint64_t>(ws, L.t0u) : t0c;
     uint32_t* fstart = at<uint32_t>(ws, L.fstart);
-    uint32_t* dag_col = at<uint32_t>(ws, L.dag_col);
-    uint2* dag_rng = at<uint2>(ws, L.dag_rng);
     orient(row_off, col, u.rank, at<uint32_t>(ws, L.rcol), gu, t0u, at<TileRec>(ws, L.recs_u),
            S.n_u, at<uint32_t>(ws, L.tile_cnt), at<uint64_t>(ws, L.masks),
            at<uint64_t>(ws, L.tile_base), at<uint64_t>(ws, L.scan_tmp), s);
-    dag_ranges(u.order, fstart, S.N, dag_rng, s);
-    sort_rows(dag_rng, S.N, dag_col, at<uint32_t>(ws, L.sort_lists),
+    sort_rows(fstart, u.rank, S.N, at<uint2>(ws, L.dag_rng), at<uint32_t>(ws, L.dag_col),
+              at<uint32_t>(ws, L.fence), at<uint32_t>(ws, L.sort_lists),
               at<uint32_t>(ws, L.sort_counts), num_cu, s);
-    fence_samples(dag_col, S.NNZ / 2, at<uint32_t>(ws, L.fence), s);
     prof_end(profile, s);
     prof_begin(profile, "triangles", s);
     TriArgs a = tri_args(S, L, knobs, ws, row_off, col);

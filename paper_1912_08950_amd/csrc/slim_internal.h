@@ -107,8 +107,6 @@ void orient(const int64_t* row_off, const uint32_t* col, const uint32_t* rank, u
             const GDesc* gd_union, const uint64_t* tile0, const TileRec* recs, uint64_t ntiles,
             uint32_t* tile_cnt, uint64_t* masks, uint64_t* tile_base, uint64_t* scan_tmp,
             hipStream_t s);
-void dag_ranges(const uint32_t* order, const uint32_t* fstart, uint64_t n, uint2* dag_rng,
-                hipStream_t s);
 // Output CSRs of every graph of the set: TR graphs keep the entries whose
 // edge is unmarked, ES graphs the entries whose edge is not sampled out.
 // eid/del may be NULL when the set has no TR graph.  masks: kChunks words per
@@ -129,16 +127,15 @@ void validate_offsets(const int64_t* row_off, uint64_t n, uint64_t nnz, uint32_t
 void validate_entries(const int64_t* row_off, const uint32_t* col, uint64_t n,
                       const TileRec* recs, uint64_t ntiles, uint32_t* err, hipStream_t s);
 
-// Every DAG row is sorted by rank id (slim_sort.hip); rows of length up to
-// kSortMin by one thread each.
-constexpr uint32_t kSortMin = 32;
-void sort_rows(const uint2* dag_rng, uint64_t n, uint32_t* dag_col, uint32_t* lists,
-               uint32_t* counts, int num_cu, hipStream_t s);
-// fence[q] = dag_col[kFenceStep * q]: the first rank id of every 128-byte
+// dag_rng and the DAG rows sorted by rank id (slim_sort.hip), with the fence:
+// fence[q] = dag_col[kFenceStep * q], the first rank id of every 128-byte
 // line of the sorted DAG columns, so that a search for a rank id in a DAG
-// row reads the row's samples and then a single line of dag_col.
+// row reads the row's samples and then a single line of dag_col.  lists: 3n
+// words, counts: 3 cleared words.
 constexpr uint32_t kFenceStep = 32;
-void fence_samples(const uint32_t* dag_col, uint64_t m, uint32_t* fence, hipStream_t s);
+void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint2* dag_rng,
+               uint32_t* dag_col, uint32_t* fence, uint32_t* lists, uint32_t* counts, int num_cu,
+               hipStream_t s);
 
 // Triangle listing + selection + deletion marks (slim_tri.hip).
 struct TriArgs {

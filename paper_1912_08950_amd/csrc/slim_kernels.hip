@@ -863,21 +863,6 @@ void orient(const int64_t* row_off, const uint32_t* col, const uint32_t* rank, u
                                   nullptr, s);
 }
 
-__global__ void k_dag_rng(const uint32_t* order, const uint32_t* fstart, uint64_t n,
-                          uint2* dag_rng) {
-  for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < n;
-       x += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t u = order[x];
-    dag_rng[x] = make_uint2(fstart[u], fstart[u + 1]);
-  }
-}
-
-void dag_ranges(const uint32_t* order, const uint32_t* fstart, uint64_t n, uint2* dag_rng,
-                hipStream_t s) {
-  hipLaunchKernelGGL(k_dag_rng, dim3(grid_for(n)), dim3(kBlock), 0, s, order, fstart, n,
-                     dag_rng);
-}
-
 void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* eid,
                  const uint32_t* del, uint64_t m, const GDesc* gd, uint32_t count,
                  const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,

@@ -2,19 +2,22 @@
 //
 // The triangle kernel finds the in-neighbour edge (y,x) inside out(y) by
 // binary search and scans only the part of out(y) ranked above x, which is
-// the suffix of a sorted row.  Rows of length 2..kSortMin are sorted by one
-// thread each (insertion sort in a private LDS slice), up to 2048 by one
-// wave in registers (a bitonic network over 64 lanes x E values: pairs
-// within a lane are exchanged in registers, pairs across lanes by a lane
-// shuffle, so no LDS traffic and no barrier), up to 4096 by one block in
-// LDS, longer rows by one block in global memory.
+// the suffix of a sorted row.  Rows of up to kSortShort entries are sorted by
+// one thread each in registers, rows up to 2048 by one wave in registers (a
+// bitonic network over 64 lanes x E values: pairs within a lane are exchanged
+// in registers, pairs across lanes by a lane shuffle, so no LDS traffic and no
+// barrier), up to 4096 by one block in LDS, longer rows by one block in global
+// memory.  Whoever sorts a row also writes the fence samples of the line
+// starts inside it.
 #include "slim_internal.h"
 
 namespace slim {
 
+constexpr uint32_t kSortShort = 32;
 constexpr uint32_t kWaveSortMax = 2048;
 constexpr uint32_t kBlockSortMax = 4096;
 constexpr uint32_t kPad = 0xffffffffu;  // larger than every rank id (n <= 2^32-1)
+constexpr int kLongBlock = 1024;
 
 __device__ __forceinline__ uint32_t pow2_ceil(uint32_t v) {
   uint32_t p = 1;
@@ -22,56 +25,138 @@ __device__ __forceinline__ uint32_t pow2_ceil(uint32_t v) {
   return p;
 }
 
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Sorted entry v at DAG position pos.
+__device__ __forceinline__ void put_sorted(uint32_t* dag_col, uint32_t* fence, uint32_t pos,
+                                           uint32_t v) {
+  dag_col[pos] = v;
+  if (pos % kFenceStep == 0) fence[pos / kFenceStep] = v;
 }
 
-// Sort short rows in place (one thread each) and classify the others:
-// wave_list gets rows for the wave sort, block_list for the block sort,
-// huge_list for the global sort; counts[0..2] their lengths.
-__global__ __launch_bounds__(kBlock) void k_sort_classify(const uint2* dag_rng, uint64_t n,
-                                                          uint32_t* dag_col, uint32_t* wave_list,
-                                                          uint32_t* block_list,
-                                                          uint32_t* huge_list, uint32_t* counts) {
-  __shared__ uint32_t slice[kBlock * (kSortMin + 1)];  // stride kSortMin+1: no bank conflicts
-  uint32_t* my = slice + threadIdx.x * (kSortMin + 1);
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
-    const uint64_t x = base + threadIdx.x;
-    uint32_t len = 0, beg = 0;
-    if (x < n) {
-      const uint2 r = dag_rng[x];
-      len = r.y - r.x;
-      beg = r.x;
-    }
-    if (len >= 2 && len <= kSortMin) {
-      for (uint32_t i = 0; i < len; ++i) {
-        const uint32_t v = dag_col[beg + i];
-        uint32_t k = i;
-        while (k > 0 && my[k - 1] > v) {
-          my[k] = my[k - 1];
-          --k;
-        }
-        my[k] = v;
-      }
-      for (uint32_t i = 0; i < len; ++i) dag_col[beg + i] = my[i];
-    }
-    const bool cls[3] = {len > kSortMin && len <= kWaveSortMax,
-                         len > kWaveSortMax && len <= kBlockSortMax, len > kBlockSortMax};
-    uint32_t* lists[3] = {wave_list, block_list, huge_list};
+// Bitonic sort of the row [beg, beg + len), len <= N, in one thread's
+// registers, padded with kPad; loads and stores of four entries aligned to 4
+// bytes (up to three entries past the row are read, inside the workspace).
+typedef uint32_t row4_t __attribute__((ext_vector_type(4), aligned(4)));
+template <int N>
+__device__ __forceinline__ void thread_sort(uint32_t* dag_col, uint32_t* fence, uint32_t beg,
+                                            uint32_t len) {
+  uint32_t v[N];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const uint64_t bal = __ballot(cls[c]);
-      if (bal == 0) continue;
-      const uint32_t cnt = __popcll(bal);
-      uint32_t base_idx = 0;
-      const int leader = __ffsll((unsigned long long)bal) - 1;
-      if ((int)lane_id() == leader) base_idx = atomicAdd(&counts[c], cnt);
-      base_idx = __shfl(base_idx, leader, kWave);
-      if (cls[c]) lists[c][base_idx + __popcll(bal & lanemask_lt())] = (uint32_t)x;
+  for (int i = 0; i < N; i += 4) {
+    row4_t x = {kPad, kPad, kPad, kPad};
+    if ((uint32_t)i < len) x = *reinterpret_cast<const row4_t*>(dag_col + beg + i);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[i + k] = (uint32_t)(i + k) < len ? x[k] : kPad;
+  }
+#pragma unroll
+  for (int k = 2; k <= N; k <<= 1) {
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1) {
+#pragma unroll
+      for (int r = 0; r < N; ++r) {
+        if ((r & j) != 0) continue;
+        const uint32_t lo = min(v[r], v[r | j]), hi = max(v[r], v[r | j]);
+        v[r] = (r & k) == 0 ? lo : hi;
+        v[r | j] = (r & k) == 0 ? hi : lo;
+      }
     }
+  }
+#pragma unroll
+  for (int i = 0; i < N; i += 4) {
+    if ((uint32_t)i + 4 <= len) {
+      *reinterpret_cast<row4_t*>(dag_col + beg + i) = row4_t{v[i], v[i + 1], v[i + 2], v[i + 3]};
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if ((uint32_t)(i + k) < len) dag_col[beg + i + k] = v[i + k];
+    }
+  }
+  // a row of at most 32 entries holds at most one line start
+  const uint32_t line = (beg + kFenceStep - 1) / kFenceStep * kFenceStep - beg;
+  if (line < len) {
+    uint32_t f = v[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) f = line == (uint32_t)i ? v[i] : f;
+    fence[(beg + line) / kFenceStep] = f;
+  }
+}
+static_assert(kSortShort <= kFenceStep, "one line start per short row");
+
+// DAG ranges by rank, the short rows sorted, the longer ones listed by
+// length: wave_list, block_list, huge_list, their counts in counts[0..2]
+// (one atomic per list and step of a block).  A thread sorts its row with
+// the smallest network that its wave's longest short row needs: a network of
+// 32 is 480 instructions for 64 rows, and no step waits on memory, where an
+// insertion sort in LDS was a serial chain as long as the square of the
+// wave's longest row.  Ranges, sort, lists and fence are one launch (R-MAT
+// scale 24: 0.43 ms, 1.05 ms as three launches with insertion sorts; 90001
+// vertices of degree 23: 11 us, 68 us; counting each entry's place in LDS took
+// 2.9 ms and 27 us).
+__global__ __launch_bounds__(kBlock) void k_sort_short(const uint32_t* fstart, const uint32_t* rank,
+                                                       uint64_t n, uint2* dag_rng,
+                                                       uint32_t* dag_col, uint32_t* fence,
+                                                       uint32_t* wave_list, uint32_t* block_list,
+                                                       uint32_t* huge_list, uint32_t* counts,
+                                                       uint32_t per) {
+  __shared__ uint32_t wcnt[kWavesPerBlock][3], at[3];
+  const uint32_t t = threadIdx.x, w = t / kWave;
+  uint32_t* lists[3] = {wave_list, block_list, huge_list};
+  auto listed = [](uint32_t len, int c) {
+    return c == 0   ? len > kSortShort && len <= kWaveSortMax
+           : c == 1 ? len > kWaveSortMax && len <= kBlockSortMax
+                    : len > kBlockSortMax;
+  };
+  const uint64_t step = (uint64_t)kBlock * per;
+  for (uint64_t v0 = blockIdx.x * step; v0 < n; v0 += gridDim.x * step) {
+    uint32_t cnt[3] = {0, 0, 0};
+#pragma unroll 1
+    for (uint32_t k = 0; k < per; ++k) {
+      const uint64_t v = v0 + (uint64_t)k * kBlock + t;
+      uint32_t beg = 0, len = 0;
+      if (v < n) {
+        beg = fstart[v];
+        const uint32_t e = fstart[v + 1];
+        len = e - beg;
+        dag_rng[rank[v]] = make_uint2(beg, e);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cnt[c] += __popcll(__ballot(listed(len, c)));
+      if (len > kSortShort) len = 0;
+      if (__ballot(len > 16))
+        thread_sort<32>(dag_col, fence, beg, len);
+      else if (__ballot(len > 8))
+        thread_sort<16>(dag_col, fence, beg, len);
+      else if (__ballot(len > 0))
+        thread_sort<8>(dag_col, fence, beg, len);
+    }
+    if (lane_id() == 0)
+      for (int c = 0; c < 3; ++c) wcnt[w][c] = cnt[c];
+    __syncthreads();
+    if (t < 3) {
+      uint32_t all = 0;
+      for (int i = 0; i < kWavesPerBlock; ++i) all += wcnt[i][t];
+      at[t] = all ? atomicAdd(&counts[t], all) : 0u;
+    }
+    __syncthreads();
+    if (cnt[0] | cnt[1] | cnt[2]) {
+      uint32_t pos[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        pos[c] = at[c];
+        for (uint32_t i = 0; i < w; ++i) pos[c] += wcnt[i][c];
+      }
+#pragma unroll 1
+      for (uint32_t k = 0; k < per; ++k) {
+        const uint64_t v = v0 + (uint64_t)k * kBlock + t;
+        const uint32_t len = v < n ? fstart[v + 1] - fstart[v] : 0u;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const uint64_t bal = __ballot(listed(len, c));
+          if (listed(len, c)) lists[c][pos[c] + __popcll(bal & lanemask_lt())] = (uint32_t)v;
+          pos[c] += __popcll(bal);
+        }
+      }
+    }
+    __syncthreads();  // wcnt and at are free
   }
 }
 
@@ -80,7 +165,9 @@ __global__ __launch_bounds__(kBlock) void k_sort_classify(const uint2* dag_rng, 
 // kPad past len.  Step (k, j) pairs i with i ^ j; the lower index of the pair
 // keeps the minimum where (i & k) == 0, the maximum elsewhere.
 template <int E>
-__device__ __forceinline__ void wave_sort_regs(uint32_t* row, uint32_t len) {
+__device__ __forceinline__ void wave_sort_regs(uint32_t* dag_col, uint32_t* fence, uint32_t beg,
+                                               uint32_t len) {
+  const uint32_t* row = dag_col + beg;
   const uint32_t lane = lane_id();
   uint32_t v[E];
 #pragma unroll
@@ -118,51 +205,47 @@ __device__ __forceinline__ void wave_sort_regs(uint32_t* row, uint32_t len) {
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const uint32_t i = lane * E + r;
-    if (i < len) row[i] = v[r];
+    if (i < len) put_sorted(dag_col, fence, beg + i, v[r]);
   }
 }
 
-// One wave per row (kSortMin < len <= 2048): the register sort with the
-// fewest values per lane that holds the row.
-__global__ __launch_bounds__(kBlock) void k_sort_wave(const uint2* dag_rng, uint32_t* dag_col,
-                                                      const uint32_t* list,
-                                                      const uint32_t* count) {
-  const int w = threadIdx.x / kWave;
-  const uint32_t total = *count;
-  for (uint32_t i = blockIdx.x * kWavesPerBlock + w; i < total;
-       i += gridDim.x * kWavesPerBlock) {
-    const uint2 r = dag_rng[list[i]];
-    const uint32_t len = r.y - r.x;
-    uint32_t* row = dag_col + r.x;
-    if (len <= 64)
-      wave_sort_regs<1>(row, len);
-    else if (len <= 128)
-      wave_sort_regs<2>(row, len);
-    else if (len <= 256)
-      wave_sort_regs<4>(row, len);
-    else if (len <= 512)
-      wave_sort_regs<8>(row, len);
-    else if (len <= 1024)
-      wave_sort_regs<16>(row, len);
-    else
-      wave_sort_regs<32>(row, len);
-  }
-}
-
-// One block per row (2048 < len <= 4096): bitonic sort in LDS.
-__global__ __launch_bounds__(kBlock) void k_sort_block(const uint2* dag_rng, uint32_t* dag_col,
-                                                       const uint32_t* list,
-                                                       const uint32_t* count) {
+// The listed rows, in one launch: waves take the rows of the wave list (the
+// register sort with the fewest values per lane that holds the row), then
+// blocks those of the other two.
+__global__ __launch_bounds__(kLongBlock) void k_sort_long(const uint32_t* fstart, uint32_t* dag_col,
+                                                          uint32_t* fence,
+                                                          const uint32_t* wave_list,
+                                                          const uint32_t* block_list,
+                                                          const uint32_t* huge_list,
+                                                          const uint32_t* counts) {
   __shared__ uint32_t s[kBlockSortMax];
-  const uint32_t total = *count;
-  for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
-    const uint2 r = dag_rng[list[i]];
-    const uint32_t len = r.y - r.x, P = pow2_ceil(len);
-    for (uint32_t k = threadIdx.x; k < P; k += kBlock) s[k] = k < len ? dag_col[r.x + k] : kPad;
+  const uint32_t n_wave = counts[0], n_block = counts[1], n_huge = counts[2];
+  for (uint32_t i = blockIdx.x + gridDim.x * (threadIdx.x / kWave); i < n_wave;
+       i += gridDim.x * (kLongBlock / kWave)) {
+    const uint32_t u = __builtin_amdgcn_readfirstlane(wave_list[i]);
+    const uint32_t beg = fstart[u], len = fstart[u + 1] - beg;
+    if (len <= 64)
+      wave_sort_regs<1>(dag_col, fence, beg, len);
+    else if (len <= 128)
+      wave_sort_regs<2>(dag_col, fence, beg, len);
+    else if (len <= 256)
+      wave_sort_regs<4>(dag_col, fence, beg, len);
+    else if (len <= 512)
+      wave_sort_regs<8>(dag_col, fence, beg, len);
+    else if (len <= 1024)
+      wave_sort_regs<16>(dag_col, fence, beg, len);
+    else
+      wave_sort_regs<32>(dag_col, fence, beg, len);
+  }
+  // one block per row (2048 < len <= 4096): bitonic sort in LDS
+  for (uint32_t i = blockIdx.x; i < n_block; i += gridDim.x) {
+    const uint32_t beg = fstart[block_list[i]], len = fstart[block_list[i] + 1] - beg;
+    const uint32_t P = pow2_ceil(len);
+    for (uint32_t k = threadIdx.x; k < P; k += kLongBlock) s[k] = k < len ? dag_col[beg + k] : kPad;
     __syncthreads();
     for (uint32_t k = 2; k <= P; k <<= 1) {
       for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-        for (uint32_t t = threadIdx.x; t < P / 2; t += kBlock) {
+        for (uint32_t t = threadIdx.x; t < P / 2; t += kLongBlock) {
           const uint32_t a = ((t & ~(j - 1)) << 1) | (t & (j - 1));
           const uint32_t b = a | j;
           const bool up = (a & k) == 0;
@@ -175,26 +258,21 @@ __global__ __launch_bounds__(kBlock) void k_sort_block(const uint2* dag_rng, uin
         __syncthreads();
       }
     }
-    for (uint32_t k = threadIdx.x; k < len; k += kBlock) dag_col[r.x + k] = s[k];
+    for (uint32_t k = threadIdx.x; k < len; k += kLongBlock)
+      put_sorted(dag_col, fence, beg + k, s[k]);
     __syncthreads();
   }
-}
-
-// One block per row (len > 4096): bitonic sort in place in global memory.
-// Every merge is ascending (the first step of a merge pairs i with its mirror
-// i ^ (k-1)), so the virtual +inf padding past `len` never moves and pairs
-// that reach past the end are skipped.
-__global__ __launch_bounds__(1024) void k_sort_huge(const uint2* dag_rng, uint32_t* dag_col,
-                                                    const uint32_t* list,
-                                                    const uint32_t* count) {
-  const uint32_t total = *count;
-  for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
-    const uint2 r = dag_rng[list[i]];
-    uint32_t* a = dag_col + r.x;
-    const uint32_t len = r.y - r.x, P = pow2_ceil(len);
+  // one block per row (len > 4096): bitonic sort in place in global memory.
+  // Every merge is ascending (the first step of a merge pairs i with its
+  // mirror i ^ (k-1)), so the virtual +inf padding past `len` never moves and
+  // pairs that reach past the end are skipped.
+  for (uint32_t i = blockIdx.x; i < n_huge; i += gridDim.x) {
+    const uint32_t beg = fstart[huge_list[i]], len = fstart[huge_list[i] + 1] - beg;
+    uint32_t* a = dag_col + beg;
+    const uint32_t P = pow2_ceil(len);
     for (uint32_t k = 2; k <= P; k <<= 1) {
       for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-        for (uint32_t t = threadIdx.x; t < P / 2; t += blockDim.x) {
+        for (uint32_t t = threadIdx.x; t < P / 2; t += kLongBlock) {
           const uint32_t lo = ((t & ~(j - 1)) << 1) | (t & (j - 1));
           const uint32_t hi = (j == (k >> 1)) ? (lo ^ (k - 1)) : (lo | j);
           if (hi < len) {
@@ -209,41 +287,31 @@ __global__ __launch_bounds__(1024) void k_sort_huge(const uint2* dag_rng, uint32
         __syncthreads();
       }
     }
+    for (uint32_t k = threadIdx.x; k < len; k += kLongBlock)
+      if ((beg + k) % kFenceStep == 0) fence[(beg + k) / kFenceStep] = a[k];
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_fence(const uint32_t* dag_col, uint64_t m,
-                                                  uint32_t* fence) {
-  const uint64_t nq = (m + kFenceStep - 1) / kFenceStep;
-  for (uint64_t q = blockIdx.x * (uint64_t)kBlock + threadIdx.x; q < nq;
-       q += (uint64_t)gridDim.x * kBlock)
-    fence[q] = dag_col[q * kFenceStep];
-}
-
-void fence_samples(const uint32_t* dag_col, uint64_t m, uint32_t* fence, hipStream_t s) {
-  const uint64_t nq = (m + kFenceStep - 1) / kFenceStep;
-  if (nq == 0) return;
-  uint64_t g = (nq + kBlock - 1) / kBlock;
-  if (g > 65536) g = 65536;
-  hipLaunchKernelGGL(k_fence, dim3((unsigned)g), dim3(kBlock), 0, s, dag_col, m, fence);
-}
-
-void sort_rows(const uint2* dag_rng, uint64_t n, uint32_t* dag_col, uint32_t* lists,
-               uint32_t* counts, int num_cu, hipStream_t s) {
+void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint2* dag_rng,
+               uint32_t* dag_col, uint32_t* fence, uint32_t* lists, uint32_t* counts, int num_cu,
+               hipStream_t s) {
   uint32_t* wave_list = lists;
   uint32_t* block_list = lists + n;
   uint32_t* huge_list = lists + 2 * n;
-  unsigned g = (unsigned)((n + kBlock - 1) / kBlock);
-  if (g > 8192) g = 8192;
+  // rows per thread and step: four share the list atomics of a large graph,
+  // one spreads a small one over the CUs
+  const uint32_t per = n >= (1u << 18) ? 4 : 1;
+  uint64_t g = (n + kBlock * per - 1) / (kBlock * per);
+  if (g > 16384) g = 16384;
   if (g < 1) g = 1;
-  hipLaunchKernelGGL(k_sort_classify, dim3(g), dim3(kBlock), 0, s, dag_rng, n, dag_col,
-                     wave_list, block_list, huge_list, counts);
-  hipLaunchKernelGGL(k_sort_wave, dim3(num_cu * 8), dim3(kBlock), 0, s, dag_rng, dag_col,
-                     wave_list, counts + 0);
-  hipLaunchKernelGGL(k_sort_block, dim3(num_cu * 4), dim3(kBlock), 0, s, dag_rng, dag_col,
-                     block_list, counts + 1);
-  hipLaunchKernelGGL(k_sort_huge, dim3(num_cu), dim3(1024), 0, s, dag_rng, dag_col, huge_list,
-                     counts + 2);
+  hipLaunchKernelGGL(k_sort_short, dim3((unsigned)g), dim3(kBlock), 0, s, fstart, rank, n, dag_rng,
+                     dag_col, fence, wave_list, block_list, huge_list, counts, per);
+  // no more blocks than a small graph can keep busy
+  uint64_t gl = (uint64_t)(num_cu > 0 ? num_cu : 256) * 2;
+  if (gl > n / kSortShort) gl = n / kSortShort;
+  if (gl < 1) return;  // a row has fewer than n entries: none is over kSortShort
+  hipLaunchKernelGGL(k_sort_long, dim3((unsigned)gl), dim3(kLongBlock), 0, s, fstart, dag_col,
+                     fence, wave_list, block_list, huge_list, counts);
 }
 
 }  // namespace slim

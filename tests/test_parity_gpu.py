@@ -555,3 +555,18 @@ def test_compaction_boundaries(slim, entries, op):
             assert np.array_equal(slim.weights_numpy(bufs), ow), g.name
         else:
             assert_same(gpu_run(slim, g, op, 0.5, 5), oracle_run(g, op, 0.5, 5), g.name)
+
+
+@pytest.mark.parametrize("k", [3, 4, 7, 8, 9, 10, 16, 17, 18, 32, 33, 34, 64, 65, 66, 129, 130])
+def test_dag_rows_of_the_register_sorts(slim, k):
+    """Cliques of k vertices: DAG rows of 0 to k - 1 entries, across the
+    networks of 8, 16 and 32 values per thread and the wave sorts of 64 and
+    128, at positions of every remainder by the fence step (several cliques
+    behind one another, vertex ids shuffled)."""
+    n = 5 * k
+    ids = np.random.default_rng(k).permutation(n)
+    pairs = [(int(ids[c * k + i]), int(ids[c * k + j]))
+             for c in range(5) for i in range(k) for j in range(i + 1, k)]
+    g = gg.from_pairs(n, pairs, f"5xK{k}")
+    for op in ("tr", "es"):
+        assert_same(gpu_run(slim, g, op, 0.6, 7), oracle_run(g, op, 0.6, 7), f"{g.name} {op}")
