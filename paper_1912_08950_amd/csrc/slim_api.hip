@@ -99,6 +99,7 @@ SetShape single_shape(uint64_t n, uint64_t nnz, int op) {
   S.N = n;
   S.NNZ = nnz;
   S.gathered = false;
+  S.kinds = 1u << out_kind(op);
   S.has_tr = op_lists_triangles((uint32_t)op);
   S.has_eo = op == SLIM_OP_EOTR;
   S.has_list = S.has_tr && !S.has_eo;
@@ -295,7 +296,7 @@ void finish_set(const SetShape& S, const SetLayout& L, void* ws, const int64_t* 
               at<GDesc>(ws, L.gd), S.count, at<uint64_t>(ws, L.t0c), at<TileRec>(ws, L.recs_c),
               S.n_c, S.most_c, at<uint32_t>(ws, L.tile_cnt), at<uint64_t>(ws, L.masks),
               at<uint64_t>(ws, L.tile_base), at<uint64_t>(ws, L.scan_tmp),
-              tr ? at<uint64_t>(ws, L.counters) : nullptr, s);
+              tr ? at<uint64_t>(ws, L.counters) : nullptr, S.kinds, s);
 }
 
 // Enqueues every phase of a set.  The header (descriptors and tile prefixes)
@@ -324,6 +325,11 @@ void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num
     std::memcpy(u.hdr, hdr, hdr_bytes);
     u.hdr_words = hdr_bytes / 4;
     u.hdr_dst = at<uint32_t>(ws, L.gd);
+    const GDesc& d = *static_cast<const GDesc*>(hdr);
+    if (d.op == SLIM_OP_SPECTRAL) {  // its output offsets hold the thresholds until the scatter
+      u.thr = static_cast<uint32_t*>(d.out_row);
+      u.ups = d.ups;
+    }
   }
   u.row_off = row_off;
   u.n = S.N;

@@ -22,6 +22,7 @@ constexpr uint64_t kTriTileMin = 256;  // smallest triangle tile (workspace is s
 
 struct SetShape {
   uint32_t count = 0;
+  uint32_t kinds = 0;       // bit out_kind(op) of each graph's operation
   uint64_t N = 0, NNZ = 0;  // union vertices and CSR entries
   bool gathered = false;    // union built in the workspace (batches)
   bool has_tr = false;      // some graph lists triangles (TR, TR2, MCTR, EOTR)

@@ -44,6 +44,7 @@ int plan_set(const std::vector<GDesc>& graphs, SetPlan& P) {
     for (int i = 0; i < 3; ++i) S.n_tri[i] += tiles_of(d.ne, kTriTileMin << i);
     S.nvt += (d.nv + kTile - 1) / kTile;
     S.net += (d.ne + kTile - 1) / kTile;
+    S.kinds |= 1u << out_kind((int)d.op);
     if (op_lists_triangles(d.op)) S.has_tr = true;
     if (d.op == SLIM_OP_TR2 || d.op == SLIM_OP_MCTR) S.general = true;
     if (d.op == SLIM_OP_MCTR) S.has_mc = true;

@@ -80,7 +80,7 @@ struct FillJob {  // p[0 .. quads) = {v, v, v, v}
 };
 constexpr int kMaxRecs = 3, kMaxFills = 1;
 constexpr int kJobHeader = 0, kJobRank = 1, kJobRecs = 2, kJobFill = kJobRecs + kMaxRecs;
-constexpr int kSetupJobs = kJobFill + kMaxFills;
+constexpr int kJobThr = kJobFill + kMaxFills, kSetupJobs = kJobThr + 1;
 struct SetupArgs {
   uint32_t hdr[96];  // header of a one-graph set, hdr_words long (0: none)
   uint32_t hdr_words;
@@ -92,6 +92,8 @@ struct SetupArgs {
   uint32_t* rank;
   RecJob rec[kMaxRecs];
   FillJob fill[kMaxFills];
+  uint32_t* thr;  // spectral keep threshold of each vertex (NULL: none), for upsilon ups
+  double ups;
   uint32_t nb[kSetupJobs];  // blocks per job, set by setup()
 };
 void setup(SetupArgs& a, hipStream_t s);
@@ -115,13 +117,15 @@ void orient(const int64_t* row_off, const uint32_t* col, const uint32_t* rank, u
 // (32 bytes -> one word).
 void pack_marks(const uint8_t* marks, uint32_t* del, uint64_t m, hipStream_t s);
 // The last tile of a graph writes its counters (2 per graph in `counters`, or
-// NULL) to its stats.  most_tiles: tiles of the largest graph.
+// NULL) to its stats.  most_tiles: tiles of the largest graph; kinds: bit
+// out_kind(op) of every graph's operation.
+inline uint32_t out_kind(int op) { return op == SLIM_OP_ES ? 1u : op == SLIM_OP_SPECTRAL ? 2u : 0u; }
 constexpr uint64_t kSelfScan = 8192;
 void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* eid,
                  const uint32_t* del, uint64_t m, const GDesc* gd, uint32_t count,
                  const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
                  uint32_t* tile_cnt, uint64_t* masks, uint64_t* tile_base, uint64_t* scan_tmp,
-                 const uint64_t* counters, hipStream_t s);
+                 const uint64_t* counters, uint32_t kinds, hipStream_t s);
 void validate_offsets(const int64_t* row_off, uint64_t n, uint64_t nnz, uint32_t* err,
                       hipStream_t s);
 void validate_entries(const int64_t* row_off, const uint32_t* col, uint64_t n,

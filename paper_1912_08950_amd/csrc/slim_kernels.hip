@@ -338,6 +338,26 @@ void degree_rank(const int64_t* row_off, uint64_t n, uint32_t* classes, uint32_t
                      (const uint32_t*)classes, classes + kDegClasses, order, rank);
 }
 
+// ------------------------------------------------ spectral thresholds
+// Keep probability of an edge whose smaller degree is d (section 4.2.1).
+__device__ __forceinline__ double spectral_p(double ups, uint32_t d) {
+  const double pe = ups / (double)d;
+  return pe > 1.0 ? 1.0 : pe;
+}
+__device__ __forceinline__ uint64_t spectral_thr(double ups, uint32_t d) {
+  const double pe = spectral_p(ups, d);
+  return pe >= 1.0 ? (uint64_t(1) << 32) : (uint64_t)floor(pe * 4294967296.0);
+}
+// The threshold that an edge has if this end has the smaller degree, at most
+// 2^32 - 1.  The quotient, the product and the floor do not decrease as d
+// falls, so an edge's threshold is the larger one of its ends': one division
+// per vertex and one 4-byte gather per entry in place of a division and the
+// two offsets of the other end.
+__device__ __forceinline__ uint32_t vertex_thr(double ups, uint32_t d) {
+  const uint64_t t = d ? spectral_thr(ups, d) : 0u;
+  return t < 0xffffffffu ? (uint32_t)t : 0xffffffffu;
+}
+
 // --------------------------------------------------------- small writes
 // Copies up to 512 bytes of host data to device memory as a kernel argument,
 // so that a call can set up its descriptors without a host-to-device copy
@@ -419,6 +439,8 @@ __global__ __launch_bounds__(kBlock) void k_setup(SetupArgs a) {
     if (threadIdx.x < a.hdr_words) a.hdr_dst[threadIdx.x] = a.hdr[threadIdx.x];
   } else if (job == kJobRank) {
     rank_small(a.row_off, (uint32_t)a.n, a.order, a.rank);
+  } else if (job == kJobThr) {
+    for (uint64_t v = t; v < a.n; v += nt) a.thr[v] = vertex_thr(a.ups, degree_of(a.row_off, v));
   } else if (job < kJobFill) {
     const RecJob& r = a.rec[job - kJobRecs];
     for (uint64_t i = t; i < r.ntiles; i += nt) {
@@ -447,6 +469,7 @@ void setup(SetupArgs& a, hipStream_t s) {
   a.nb[kJobRank] = a.order && a.n <= kRankSmall && a.n ? 1 : 0;
   for (int i = 0; i < kMaxRecs; ++i) a.nb[kJobRecs + i] = blocks(a.rec[i].ntiles, 4096);
   for (int i = 0; i < kMaxFills; ++i) a.nb[kJobFill + i] = blocks(a.fill[i].quads, 1024);
+  a.nb[kJobThr] = a.thr ? blocks(a.n, 4096) : 0;
   uint64_t grid = 0;
   for (int i = 0; i < kSetupJobs; ++i) grid += a.nb[i];
   if (grid) hipLaunchKernelGGL(k_setup, dim3((unsigned)grid), dim3(kBlock), 0, s, a);
@@ -470,8 +493,13 @@ __global__ __launch_bounds__(kBlock) void k_gather(const GDesc* gd, uint32_t cou
     const uint64_t i0 = (tt - pre[g]) * kTile;
     if (vert) {
       const uint64_t i1 = i0 + kTile < G.nv ? i0 + kTile : G.nv;
-      for (uint64_t i = i0 + threadIdx.x; i < i1; i += kBlock)
+      // (a spectral graph's thresholds lie in its output offsets until the
+      // scatter pass writes those)
+      uint32_t* thr = G.op == SLIM_OP_SPECTRAL ? static_cast<uint32_t*>(G.out_row) : nullptr;
+      for (uint64_t i = i0 + threadIdx.x; i < i1; i += kBlock) {
         urow[G.vb + i] = G.in_row[i] + (int64_t)G.eb;
+        if (thr) thr[i] = vertex_thr(G.ups, degree_of(G.in_row, i));
+      }
     } else {
       const uint64_t i1 = i0 + kTile < G.ne ? i0 + kTile : G.ne;
       const uint32_t vb = (uint32_t)G.vb;
@@ -609,7 +637,16 @@ struct OrientPolicy {
 // (local ids) iff Philox(a,b,0,1) word 0 >= thr; a spectral sparsification
 // graph keeps {a<b} iff Philox(a,b,0,2) word 0 < floor(p_ab 2^32) with
 // p_ab = min(1, upsilon / min(d_a, d_b)) in double precision (section 4.2.1)
-// and weighs it 1/p_ab.  Written values are local ids.
+// and weighs it 1/p_ab.  Written values are local ids.  The count pass reads
+// a spectral graph's vertex thresholds from its output offsets, which the
+// scatter pass then overwrites (R-MAT scale 22: count pass 1.50 ms with the
+// degrees gathered and divided per entry, 1.17 ms with the thresholds).
+// kMode: the mode of every graph of the set (0 triangle operations, 1 ES, 2
+// spectral), or kMixed: a pass over one kind of graph keeps only that kind's
+// values in registers (edge sampling at R-MAT scale 24: 1.73 ms with the
+// mixed passes, 1.51 ms so).
+constexpr uint32_t kMixed = 3;
+template <uint32_t kMode>
 struct OutPolicy {
   static constexpr bool kOut = true;
   const uint32_t* col;
@@ -620,40 +657,38 @@ struct OutPolicy {
   struct Ctx {
     uint64_t thr;
     double ups;
-    uint32_t vb, k0, k1, mode;  // mode: 0 triangle ops, 1 ES, 2 spectral
+    const uint32_t* vthr;       // spectral: threshold of each vertex
+    uint32_t vb, k0, k1, any_mode;
   };
+  __device__ static uint32_t mode(const Ctx& x) { return kMode == kMixed ? x.any_mode : kMode; }
   __device__ Ctx ctx(const GDesc& G) const {
-    return Ctx{G.thr, G.ups, (uint32_t)G.vb, G.k0, G.k1,
+    return Ctx{G.thr, G.ups, static_cast<const uint32_t*>(G.out_row), (uint32_t)G.vb, G.k0, G.k1,
                G.op == SLIM_OP_ES ? 1u : (G.op == SLIM_OP_SPECTRAL ? 2u : 0u)};
   }
-  __device__ bool needs_rows(const Ctx& x) const { return x.mode != 0; }
-  __device__ const uint32_t* source(const Ctx& x) const { return x.mode ? col : eid; }
+  __device__ bool needs_rows(const Ctx& x) const { return mode(x) != 0; }
+  __device__ const uint32_t* source(const Ctx& x) const { return mode(x) ? col : eid; }
   __device__ uint32_t fetch(const Ctx& x, uint32_t v) const {
-    if (x.mode == 0) return v < m ? del[v >> 5] : 0u;  // v >= m only for inputs breaking the contract
-    if (x.mode == 2) return degree_of(row_off, v);
+    if (mode(x) == 0) return v < m ? del[v >> 5] : 0u;  // v >= m only for inputs breaking the contract
+    if (mode(x) == 2) return x.vthr[v - x.vb];
     return 0u;
   }
-  // keep probability of the spectral scheme by the smaller degree
-  __device__ double spectral_p(const Ctx& x, uint32_t dmin) const {
-    const double pe = x.ups / (double)dmin;
-    return pe > 1.0 ? 1.0 : pe;
-  }
   __device__ bool flag(const Ctx& x, uint32_t v, uint32_t got, uint32_t r) const {
-    if (x.mode == 0) return v >= m || !((got >> (v & 31u)) & 1u);
+    if (mode(x) == 0) return v >= m || !((got >> (v & 31u)) & 1u);
     const uint32_t c = v - x.vb, rl = r - x.vb;
     const uint32_t a = min(c, rl), b = max(c, rl);
     uint32_t w0, w1;
-    philox_w01(a, b, 0u, x.mode, x.k0, x.k1, w0, w1);
-    if (x.mode == 1) return !((uint64_t)w0 < x.thr);
-    const double pe = spectral_p(x, min(got, degree_of(row_off, r)));
-    const uint64_t thr = pe >= 1.0 ? (uint64_t(1) << 32) : (uint64_t)floor(pe * 4294967296.0);
-    return (uint64_t)w0 < thr;
+    philox_w01(a, b, 0u, mode(x), x.k0, x.k1, w0, w1);
+    if (mode(x) == 1) return !((uint64_t)w0 < x.thr);
+    const uint32_t thr = max(got, x.vthr[rl]);
+    if (w0 < thr || thr != 0xffffffffu) return w0 < thr;
+    // w0 is 2^32 - 1: only a threshold of 2^32 keeps it
+    return spectral_thr(x.ups, min(degree_of(row_off, v), degree_of(row_off, r))) >> 32;
   }
   __device__ void stream(const Ctx&, int64_t, uint32_t, const uint32_t (&)[4]) const {}
   __device__ const uint32_t* values(const Ctx&) const { return col; }
   __device__ uint32_t value(const Ctx& x, uint32_t v) const { return v - x.vb; }
   __device__ float weight(const Ctx& x, uint32_t c, uint32_t r) const {
-    return (float)(1.0 / spectral_p(x, min(degree_of(row_off, c), degree_of(row_off, r))));
+    return (float)(1.0 / spectral_p(x.ups, min(degree_of(row_off, c), degree_of(row_off, r))));
   }
 };
 
@@ -867,10 +902,18 @@ void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* ei
                  const uint32_t* del, uint64_t m, const GDesc* gd, uint32_t count,
                  const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
                  uint32_t* tile_cnt, uint64_t* masks, uint64_t* tile_base, uint64_t* scan_tmp,
-                 const uint64_t* counters, hipStream_t s) {
-  OutPolicy p{col, eid, del, row_off, m};
-  compact<OutPolicy, int64_t>(p, row_off, gd, count, tile0, recs, ntiles, most_tiles <= kSelfScan,
-                              tile_cnt, masks, tile_base, scan_tmp, counters, s);
+                 const uint64_t* counters, uint32_t kinds, hipStream_t s) {
+  auto go = [&](auto policy) {
+    compact<decltype(policy), int64_t>(policy, row_off, gd, count, tile0, recs, ntiles,
+                                       most_tiles <= kSelfScan, tile_cnt, masks, tile_base,
+                                       scan_tmp, counters, s);
+  };
+  switch (kinds) {
+    case 1u << 0: go(OutPolicy<0>{col, eid, del, row_off, m}); break;
+    case 1u << 1: go(OutPolicy<1>{col, eid, del, row_off, m}); break;
+    case 1u << 2: go(OutPolicy<2>{col, eid, del, row_off, m}); break;
+    default: go(OutPolicy<kMixed>{col, eid, del, row_off, m});
+  }
 }
 
 // ------------------------------------------------------------ validation
