@@ -73,8 +73,9 @@ constexpr int kEntries = kTT / kTB;  // consecutive tile entries per thread
 constexpr int kWavesPerEU = 2 * kTW / 4;  // two resident blocks per CU (LDS), four SIMDs
 constexpr int kHashCap = 2048;       // out-list entries hashed per pass
 constexpr int kHashPer = kHashCap / kTB;  // most hashed entries per thread
-constexpr int kSlotBits = 12;        // one-entry slots of the hash (load <= 1/2)
-constexpr int kSlots = 1 << kSlotBits;
+constexpr int kPosBits = 11;         // bits of a position in the hashed range
+constexpr int kBucketBits = 10;      // hash buckets of four slots (load <= 1/2)
+constexpr int kBuckets = 1 << kBucketBits;
 constexpr int kFiltWords = 2048;     // words of the filter: 65536 bits
 constexpr int kQ = 128;              // per-wave candidate stack (records)
 constexpr int kItemBits = 17;        // scan items of one mask pass: at most 2^17
@@ -86,7 +87,7 @@ constexpr uint32_t kEmpty = 0xffffffffu;
 constexpr uint32_t kDead = 0xffffffffu;  // Edge-Once list record of a decided triangle
 
 static_assert(kEntries * kTB == kTT && kEntries == 2, "two tile entries per thread");
-static_assert(kHashCap <= kSlots / 2 && kHashCap < (1 << kSlotBits) - 1, "position fits the slot's low bits");
+static_assert(kHashCap <= 2 * kBuckets && kHashCap <= (1 << kPosBits), "a position fits a slot's low bits");
 
 // In-edges per batch (kB) and words of the in-edge mask (kM) of each
 // instantiation: as many as two blocks per CU allow in LDS; the general and
@@ -114,9 +115,8 @@ struct TriSmem {
   static_assert(kM * kWave * kQuad <= (1 << kItemBits) && kB <= (1 << (32 - kItemBits)),
                 "a candidate's in-edge and item share one word");
   uint32_t filt[kFiltWords];  // bit set: some hashed key may have it
-  uint32_t slot[kSlots];      // (hash << kSlotBits) | position in range, or kEmpty
-  uint32_t xw[kHashCap];      // rank id and original (local) id of each hashed
-  uint32_t xold[kHashCap];    //   out-list entry
+  uint4 bucket[kBuckets];     // slots: (hash << kPosBits) | position in range, or kEmpty
+  uint2 xw[kHashCap];         // {rank id, original (local) id} of each hashed entry
   uint8_t xflag[kHashCap];    // deletion mark of each hashed entry
   uint32_t srow[kTT];  // row of each tile entry (after the max-scan)
   uint16_t bw[kTT];    // local indices of the tile's backward entries, in order, and,
@@ -161,8 +161,9 @@ struct TriSmemEO {
 
 // A key is (w, row); rows are told apart by the position rs of their first
 // entry in the hashed range.  Its 32-bit hash w * A + rs * B gives the home
-// slot (top 12 bits, then linear probing), the 20 low bits kept beside the
-// position in the slot, and the filter's word (top 11 bits) and bit (low 5).
+// bucket (top 10 bits; a full bucket's keys go on to the next one), the 21 low
+// bits kept beside the position in a slot, and the filter's word (top 11 bits)
+// and bit (low 5).
 __device__ __forceinline__ uint32_t hrow(uint32_t rs) { return rs * 0x85EBCA6Bu; }
 __device__ __forceinline__ uint32_t hkey(uint32_t w, uint32_t row) {
   return (uint32_t)((uint64_t)w * 0x9E3779B1u + row);  // one multiply-add
@@ -174,22 +175,44 @@ __device__ __forceinline__ bool hfilter(const uint32_t* filt, uint32_t h) {
   return (int32_t)(v << (h & 31u)) < 0;
 }
 
+// The hash bits of a slot, never all ones above a position (kEmpty is no key).
+__device__ __forceinline__ uint32_t hslot(uint32_t h) { return min(h << kPosBits, 0xfffff000u); }
+
 // Exact look-up of w, of hash h, in the row of positions [rsl & 0xffff, +
-// (rsl >> 16)).  Slots fill in probe order, are never removed and are at most
-// half full, so the walk ends at the key or at an empty slot.
+// (rsl >> 16)); pair: {rank id, local id} of the entry at qpos.  Slots fill in
+// order and are never removed, so the key is in its home bucket unless that
+// is full.  A slot whose hash bits agree differs from them by a position, any
+// other by more: the smallest difference of the four is the one to verify.
+// Only a verified key counts; where the smallest one is another key's (its 21
+// bits agree) or the bucket is full, every slot from there on is verified.
+// (With one-entry slots and linear probing 64 look-ups took two to three
+// rounds of two dependent LDS reads.)
 template <class Smem>
 __device__ __forceinline__ bool hfind(const Smem& S, uint32_t w, uint32_t h, uint32_t rsl,
-                                      uint32_t& qpos) {
-  uint32_t b = h >> (32 - kSlotBits);
-  const uint32_t hl = h << kSlotBits, rs = rsl & 0xffffu, len = rsl >> 16;
-  bool hit, go;
-  do {  // straight-line: an empty slot's q fails the range test (q >= kHashCap or the fingerprint)
-    const uint32_t v = S.slot[b], q = v ^ hl;
-    hit = (S.xw[q & (kHashCap - 1)] == w) & (q - rs < len);
-    qpos = q & (kHashCap - 1);
-    go = !hit & (v != kEmpty);
-    b = (b + 1) & (kSlots - 1);
-  } while (go);
+                                      uint32_t& qpos, uint2& pair) {
+  uint32_t b = h >> (32 - kBucketBits);
+  const uint32_t hs = hslot(h), rs = rsl & 0xffffu, len = rsl >> 16;
+  const uint4 s = S.bucket[b];
+  const uint32_t q = min(min(s.x ^ hs, s.y ^ hs), min(s.z ^ hs, s.w ^ hs));
+  qpos = q & (kHashCap - 1);
+  pair = S.xw[qpos];
+  // positions past the range (q >= kHashCap: no hash bits agree) fail the row test
+  bool hit = (pair.x == w) & (q - rs < len);
+  if (!hit & ((q < (uint32_t)kHashCap) | (s.w != kEmpty))) {  // rare
+    for (;;) {
+      const uint4 v = S.bucket[b];
+      const uint32_t c[4] = {v.x ^ hs, v.y ^ hs, v.z ^ hs, v.w ^ hs};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (c[i] < (uint32_t)kHashCap && c[i] - rs < len && S.xw[c[i]].x == w) {
+          qpos = c[i];
+          hit = true;
+        }
+      if (hit | (v.w == kEmpty)) break;
+      b = (b + 1) & (kBuckets - 1);
+    }
+    if (hit) pair = S.xw[qpos];
+  }
   return hit;
 }
 
@@ -260,12 +283,12 @@ template <class Smem>
 __device__ __forceinline__ void tri_clear_hash(Smem& S) {
   const int tid = threadIdx.x;
 #pragma unroll
-  for (int i = 0; i < kSlots / 4; i += kTB)
-    reinterpret_cast<uint4*>(S.slot)[i + tid] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+  for (int i = 0; i < kBuckets; i += kTB)
+    S.bucket[i + tid] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
   reinterpret_cast<uint4*>(S.filt)[tid] = make_uint4(0u, 0u, 0u, 0u);
   reinterpret_cast<uint32_t*>(S.xflag)[tid] = 0;
 }
-static_assert(kSlots / 4 % kTB == 0 && kFiltWords / 4 == kTB && kHashCap / 4 == kTB,
+static_assert(kBuckets % kTB == 0 && kFiltWords / 4 == kTB && kHashCap / 4 == kTB,
               "whole vectors per thread");
 
 // Hash the out-list entries [D0, D0 + len) into the cleared hash.  A thread
@@ -309,8 +332,7 @@ __device__ void tri_build_hash(TriCtx& C, Smem& S, uint32_t len, bool all_rows) 
   for (uint32_t i = 0; i < (uint32_t)kHashPer; ++i) {
     const uint32_t q = q0 + i;
     if (i >= per || q >= len) break;
-    S.xw[q] = w[i];
-    S.xold[q] = o[i] - C.vb;
+    S.xw[q] = make_uint2(w[i], o[i] - C.vb);
     if (C.xmin) C.xmin[q] = 0xffffffffu;
     // counts exist only for Min-Count graphs: loaded for their selection
     // pass, zeroed for their counting pass (other operations never read them)
@@ -320,8 +342,9 @@ __device__ void tri_build_hash(TriCtx& C, Smem& S, uint32_t len, bool all_rows) 
     if (skip_closed && bit_get(C.a.closed, C.D0 + q)) continue;
     const uint32_t h = hkey(w[i], hrow(g[i]));
     atomicOr(&S.filt[h >> 21], 0x80000000u >> (h & 31u));
-    uint32_t b = h >> (32 - kSlotBits);
-    while (atomicCAS(&S.slot[b], kEmpty, (h << kSlotBits) | q) != kEmpty) b = (b + 1) & (kSlots - 1);
+    uint32_t* slots = reinterpret_cast<uint32_t*>(S.bucket);
+    uint32_t at = (h >> (32 - kBucketBits)) * 4;  // slot by slot through the buckets
+    while (atomicCAS(&slots[at], kEmpty, hslot(h) | q) != kEmpty) at = (at + 1) & (4 * kBuckets - 1);
   }
   C.hlen = len;
   __syncthreads();
@@ -366,7 +389,8 @@ __device__ void tri_forward_eids(TriCtx& C, Smem& S, uint32_t nfw, uint32_t ia, 
       len = C.a.fstart[S.srow[i] + 1] - fs;
     }
     uint32_t qpos;
-    if (hfind(S, w, hkey(w, hrow(rs)), rs | (len << 16), qpos)) C.a.eid[j] = C.D0 + qpos;
+    uint2 pair;
+    if (hfind(S, w, hkey(w, hrow(rs)), rs | (len << 16), qpos, pair)) C.a.eid[j] = C.D0 + qpos;
   }
 }
 
@@ -404,10 +428,10 @@ __device__ __forceinline__ bool tri_lookup(const Smem& S, uint2 rec, uint32_t it
   t.p_yw = sc.x + item;
   t.y = tr.y;
   t.x = tr.z;
-  t.qpos = 0;
   // items past the in-edge's end fill up its last quad
-  const bool hit = item < tr.x && hfind(S, rec.x, hkey(rec.x, sc.y), tr.w, t.qpos);
-  t.w = S.xold[t.qpos];
+  uint2 pair;
+  const bool hit = item < tr.x && hfind(S, rec.x, hkey(rec.x, sc.y), tr.w, t.qpos, pair);
+  t.w = pair.y;
   return hit;
 }
 
