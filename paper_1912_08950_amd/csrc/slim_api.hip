@@ -255,13 +255,11 @@ void eo_rounds(const SetShape& S, const SetLayout& L, const Tuning& knobs, int n
   for (uint32_t r = r0; r <= r1; ++r) {
     a.round = r;
     uint32_t* ctr = at<uint32_t>(ws, L.tri_ctr) + 2;
-    eo_round_start(a, ctr, s);
-    eo_clear_bids(a.minkey, a.closed, S.NNZ / 2, a.eo_und, a.eo_state, a.eo_list_cnt, r, s);
-    eo_list_clear(a, num_cu, s);
+    eo_begin(a, S.NNZ / 2, ctr, num_cu, s);
     a.pass = 2;
     triangles(a, kModeEO, ctr, num_cu, knobs.tri_blocks_per_cu, knobs.tri_chunk, s);
-    eo_accept_edges(a, S.N, num_cu, s);
-    eo_list_round(a, num_cu, s);
+    eo_list_bids(a, S.NNZ / 2, num_cu, s);
+    eo_accept(a, S.NNZ / 2, S.N, num_cu, s);
   }
 }
 

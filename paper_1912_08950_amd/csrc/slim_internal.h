@@ -214,25 +214,17 @@ constexpr uint64_t kEoListPerEdge = 3;
 // records when there are at most this many (three random stores each),
 // instead of sweeping every edge.
 constexpr uint64_t kEoListClearMax = 1ull << 23;
-void eo_clear_bids(uint64_t* minkey, uint32_t* closed, uint64_t m, const uint64_t* eo_und,
-                   const uint32_t* eo_state, const uint64_t* eo_list_cnt, uint32_t round,
-                   hipStream_t s);
-// Acceptance of round a.round by an edge-parallel kernel over the n union
-// vertices (returns at once once the triangles are listed).
-void eo_accept_edges(const TriArgs& a, uint64_t n, int num_cu, hipStream_t s);
-// Start of round a.round: a list that the previous round started but
-// overflowed is dropped (the round accepted by the edge-parallel kernel).
-void eo_round_start(const TriArgs& a, uint32_t* tile_ctr, hipStream_t s);
-// Clears the bids of the previous round through its list records, when the
-// round runs on the lists and they are few (k_eo_clear_bids sweeps otherwise).
-void eo_list_clear(const TriArgs& a, int num_cu, hipStream_t s);
-// Bids and acceptance of round a.round on the triangle lists (both return
-// at once unless the list was started in an earlier round; acceptance also
-// in the listing round).  Round r after the listing round L bids from list
-// (r - L - 1) mod 2 and copies the triangles that bid into the other list,
-// which its acceptance then reads; the listing round's acceptance reads
-// list 0.
-void eo_list_round(const TriArgs& a, int num_cu, hipStream_t s);
+// The launches of round a.round over m DAG edges and n union vertices, with
+// the bidding pass of triangles() behind the first: drop of an overflowed
+// list, reset of the bids and of the tile counter; bids on the triangle list
+// (returns at once unless the list was started in an earlier round);
+// acceptance, on the list or by the edges.  Round r after the listing round L
+// bids from list (r - L - 1) mod 2 and copies the triangles that bid into the
+// other list, which its acceptance then reads; the listing round's acceptance
+// reads list 0.
+void eo_begin(const TriArgs& a, uint64_t m, uint32_t* tile_ctr, int num_cu, hipStream_t s);
+void eo_list_bids(const TriArgs& a, uint64_t m, int num_cu, hipStream_t s);
+void eo_accept(const TriArgs& a, uint64_t m, uint64_t n, int num_cu, hipStream_t s);
 
 // Scheduling knobs; never change results.
 struct Tuning {

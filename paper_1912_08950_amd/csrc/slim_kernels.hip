@@ -44,49 +44,6 @@ void fill_i64(int64_t* p, uint64_t len, int64_t v, hipStream_t s) {
   if (len) hipLaunchKernelGGL(k_fill_i64, dim3(grid_for(len)), dim3(kBlock), 0, s, p, len, v);
 }
 
-// ---------------------------------------------------- Edge-Once bids
-// Start of Edge-Once round `round`: from the second round on, an edge that
-// no undecided triangle bid on in the previous round is closed (every
-// selected triangle on it is decided); then every bid is reset.  A wave
-// takes 64 edges, so the two bitmap words of its chunk are its own.
-__global__ void k_eo_clear_bids(uint64_t* minkey, uint32_t* closed, uint64_t m,
-                                const uint64_t* eo_und, const uint32_t* eo_state,
-                                const uint64_t* eo_list_cnt, uint32_t round) {
-  if (round > 1 && eo_und[round - 1] == 0) return;  // the rounds have ended
-  // a round on the lists whose previous bidders are few clears their bids
-  // through their list records (k_eo_list_clear); every edge of an
-  // undecided triangle got a bid then, so closing unbid edges is moot
-  const uint32_t listed = eo_state[0];
-  if (listed != 0 && listed < round &&
-      eo_list_cnt[(round - listed - 1) & 1u] <= kEoListClearMax)
-    return;
-  const uint32_t lane = lane_id();
-  const uint64_t waves = (uint64_t)gridDim.x * kWavesPerBlock;
-  for (uint64_t c = blockIdx.x * (uint64_t)kWavesPerBlock + threadIdx.x / kWave;
-       c * kWave < m; c += waves) {
-    const uint64_t i = c * kWave + lane;
-    bool dead = false;
-    if (i < m) {
-      dead = round > 1 && minkey[i] == ~0ull;
-      minkey[i] = ~0ull;
-    }
-    const uint64_t bal = __ballot(dead);
-    if (lane == 0 && bal) {
-      closed[2 * c] |= (uint32_t)bal;
-      closed[2 * c + 1] |= (uint32_t)(bal >> 32);
-    }
-  }
-}
-
-void eo_clear_bids(uint64_t* minkey, uint32_t* closed, uint64_t m, const uint64_t* eo_und,
-                   const uint32_t* eo_state, const uint64_t* eo_list_cnt, uint32_t round,
-                   hipStream_t s) {
-  if (!m) return;
-  const uint64_t chunks = (m + kWave - 1) / kWave;
-  hipLaunchKernelGGL(k_eo_clear_bids, dim3(grid_for(chunks * kWave)), dim3(kBlock), 0, s, minkey,
-                     closed, m, eo_und, eo_state, eo_list_cnt, round);
-}
-
 // --------------------------------------------------------- deletion marks
 // Word i of the bitmap gets bit b set iff byte 32i + b of the marks is set;
 // each thread reads its 32 bytes as two uint4.

@@ -1097,42 +1097,79 @@ __device__ __forceinline__ bool eo_listed_round(const TriArgs& a, bool accept) {
          (listed < a.round || (accept && listed == a.round && !eo_list_overflow(a)));
 }
 
-__global__ void k_eo_round_start(TriArgs a, uint32_t* tile_ctr) {
-  *tile_ctr = 0;
-  const uint32_t listed = a.eo_state[0];
-  if (listed != 0 && listed + 1 == a.round && eo_list_overflow(a)) {
-    a.eo_state[0] = 0;
-    a.eo_list_cnt[0] = 0;
-    a.eo_list_cnt[1] = 0;
+// Start of round a.round.  A list that the previous round started but
+// overflowed is dropped (that round accepted by the edges).  Then the bids are
+// reset: through the records of the list that this round bids from, where its
+// previous bidders are few (all of them bid on their three edges; a dead slot
+// of the listing round's list bid nowhere), else by a sweep over the edges.
+// From the second round on, the sweep closes every edge that no undecided
+// triangle bid on in the previous round: every selected triangle on it is
+// decided (every edge of a listed triangle got a bid, so the list path has
+// nothing to close).  One launch, where the drop, the two ways to reset and
+// the tile counter were four: 16 rounds of empty launches were most of a
+// small graph's call.
+__global__ __launch_bounds__(kListBlock) void k_eo_begin(TriArgs a, uint64_t m, uint32_t* tile_ctr) {
+  const bool one = blockIdx.x == 0 && threadIdx.x == 0;
+  if (one) *tile_ctr = 0;
+  // the first thread may drop the list while others look: it writes the state
+  // before the count, they read the count before the state, so whoever misses
+  // the overflow sees the state already dropped (both words are read past the
+  // caches, the first one awaited before the second; an acquire at device
+  // scope would also empty the caches once per wave: 4.1 ms instead of 0.58
+  // for a graph of 2e5 vertices)
+  const uint64_t cnt0 = __hip_atomic_load(&a.eo_list_cnt[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  uint32_t listed = __hip_atomic_load(&a.eo_state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (listed != 0 && listed + 1 == a.round && cnt0 > a.eo_cap) {
+    if (one) {
+      __hip_atomic_store(&a.eo_state[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.eo_list_cnt[1], (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.eo_list_cnt[0], (uint64_t)0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    listed = 0;
+  }
+  if (a.round > 1 && a.eo_und[a.round - 1] == 0) return;  // the rounds have ended
+  if (listed != 0 && listed < a.round) {
+    const uint32_t src = (a.round - listed - 1) & 1u;
+    uint64_t n = a.eo_list_cnt[src];
+    if (n <= kEoListClearMax) {
+      if (n > a.eo_cap) n = a.eo_cap;
+      const uint4* list = a.eo_list + (uint64_t)src * 2 * a.eo_cap;
+      for (uint64_t i = blockIdx.x * (uint64_t)kListBlock + threadIdx.x; i < n;
+           i += (uint64_t)gridDim.x * kListBlock) {
+        const uint4 r0 = list[2 * i];
+        if (r0.x == kDead) continue;
+        a.minkey[r0.x] = ~0ull;
+        a.minkey[r0.y] = ~0ull;
+        a.minkey[r0.z] = ~0ull;
+      }
+      return;
+    }
+  }
+  // a wave takes 64 edges, so the two bitmap words of its chunk are its own
+  const uint32_t lane = lane_id();
+  const uint64_t waves = (uint64_t)gridDim.x * (kListBlock / kWave);
+  for (uint64_t c = blockIdx.x * (uint64_t)(kListBlock / kWave) + threadIdx.x / kWave;
+       c * kWave < m; c += waves) {
+    const uint64_t i = c * kWave + lane;
+    bool dead = false;
+    if (i < m) {
+      dead = a.round > 1 && a.minkey[i] == ~0ull;
+      a.minkey[i] = ~0ull;
+    }
+    const uint64_t bal = __ballot(dead);
+    if (lane == 0 && bal) {
+      a.closed[2 * c] |= (uint32_t)bal;
+      a.closed[2 * c + 1] |= (uint32_t)(bal >> 32);
+    }
   }
 }
 
-// Clears the bids that the previous round's bidders placed: they are the
-// records of the list this round bids from (all of them bid on their three
-// edges; a dead slot of the listing round's list bid nowhere).
-__global__ __launch_bounds__(kListBlock) void k_eo_list_clear(TriArgs a) {
-  if (a.eo_und[a.round - 1] == 0) return;
-  const uint32_t listed = a.eo_state[0];
-  if (listed == 0 || listed >= a.round) return;
-  const uint32_t src = (a.round - listed - 1) & 1u;
-  uint64_t n = a.eo_list_cnt[src];
-  if (n > kEoListClearMax) return;  // k_eo_clear_bids swept every edge
-  if (n > a.eo_cap) n = a.eo_cap;
-  const uint4* list = a.eo_list + (uint64_t)src * 2 * a.eo_cap;
-  for (uint64_t i = blockIdx.x * (uint64_t)kListBlock + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * kListBlock) {
-    const uint4 r0 = list[2 * i];
-    if (r0.x == kDead) continue;
-    a.minkey[r0.x] = ~0ull;
-    a.minkey[r0.y] = ~0ull;
-    a.minkey[r0.z] = ~0ull;
-  }
-}
-
-// Records a wave takes at a time: it counts the ones that will bid, reserves
-// that many slots of the other list with one atomic, then bids and copies
-// them (one atomic per 64 records on the shared counter serialized the
-// kernel).
+// Records a wave takes at a time, at most: it counts the ones that will bid,
+// reserves that many slots of the other list with one atomic, then bids and
+// copies them (one atomic per 64 records on the shared counter serialized the
+// kernel).  A short list is spread over the waves, 64 records at least: a
+// chain of 16 steps took 65 us for a few thousand records.
 constexpr uint32_t kListSpan = 16 * kWave;
 
 __device__ __forceinline__ bool eo_list_live(const TriArgs& a, const uint4& r0) {
@@ -1151,9 +1188,11 @@ __global__ __launch_bounds__(kListBlock) void k_eo_list_bid(TriArgs a) {
   const uint32_t lane = lane_id();
   const uint64_t waves = (uint64_t)gridDim.x * (kListBlock / kWave);
   uint64_t und = 0;
-  for (uint64_t b = (blockIdx.x * (uint64_t)(kListBlock / kWave) + threadIdx.x / kWave) * kListSpan;
-       b < n; b += waves * kListSpan) {
-    const uint64_t e = b + kListSpan < n ? b + kListSpan : n;
+  const uint64_t share = (n / waves + kWave - 1) / kWave * kWave;
+  const uint64_t span = share < kWave ? kWave : share < kListSpan ? share : kListSpan;
+  for (uint64_t b = (blockIdx.x * (uint64_t)(kListBlock / kWave) + threadIdx.x / kWave) * span;
+       b < n; b += waves * span) {
+    const uint64_t e = b + span < n ? b + span : n;
     uint64_t cnt = 0;
     for (uint64_t i = b + lane; i < e; i += kWave) cnt += eo_list_live(a, from[2 * i]);
     cnt = wave_sum64(cnt);
@@ -1194,8 +1233,8 @@ __global__ __launch_bounds__(kListBlock) void k_eo_list_bid(TriArgs a) {
   }
 }
 
-__global__ __launch_bounds__(kListBlock) void k_eo_list_accept(TriArgs a) {
-  if (!eo_listed_round(a, true)) return;
+// Acceptance on the list.
+__device__ __forceinline__ void eo_accept_list(const TriArgs& a) {
   const uint32_t listed = a.eo_state[0];
   // the list this round's bids came from has been read in full: clear its
   // count for the next round, which copies into it
@@ -1238,11 +1277,8 @@ __device__ __forceinline__ uint32_t dag_pos(const TriArgs& a, uint32_t ru, uint3
   return lo < rg.y && a.dag_col[lo] == hi_r ? lo : kDead;
 }
 
-__global__ __launch_bounds__(kListBlock) void k_eo_accept_edges(TriArgs a, uint64_t n) {
-  const uint32_t listed = a.eo_state[0];
-  const bool on_list = listed != 0 && listed <= a.round &&
-                       !(listed == a.round && eo_list_overflow(a));
-  if (on_list || a.eo_und[a.round] == 0) return;
+__device__ __forceinline__ void eo_accept_edges(const TriArgs& a, uint64_t n) {
+  if (a.eo_und[a.round] == 0) return;
   const uint32_t lane = lane_id();
   const uint64_t waves = (uint64_t)gridDim.x * (kListBlock / kWave);
   for (uint64_t g = blockIdx.x * (uint64_t)(kListBlock / kWave) + threadIdx.x / kWave;
@@ -1297,24 +1333,29 @@ __global__ __launch_bounds__(kListBlock) void k_eo_accept_edges(TriArgs a, uint6
   }
 }
 
-void eo_accept_edges(const TriArgs& a, uint64_t n, int num_cu, hipStream_t s) {
-  const unsigned blocks = (unsigned)(num_cu > 0 ? num_cu * 8 : 2048);
-  hipLaunchKernelGGL(k_eo_accept_edges, dim3(blocks), dim3(kListBlock), 0, s, a, n);
+__global__ __launch_bounds__(kListBlock) void k_eo_accept(TriArgs a, uint64_t n) {
+  if (eo_listed_round(a, true))
+    eo_accept_list(a);
+  else
+    eo_accept_edges(a, n);
 }
 
-void eo_round_start(const TriArgs& a, uint32_t* tile_ctr, hipStream_t s) {
-  hipLaunchKernelGGL(k_eo_round_start, dim3(1), dim3(1), 0, s, a, tile_ctr);
+// Blocks for `items` items, one per thread, at most eight per CU.
+static unsigned eo_blocks(uint64_t items, int num_cu) {
+  const uint64_t most = num_cu > 0 ? (uint64_t)num_cu * 8 : 2048, b = (items + kListBlock - 1) / kListBlock;
+  return (unsigned)(b < 1 ? 1 : b < most ? b : most);
 }
 
-void eo_list_clear(const TriArgs& a, int num_cu, hipStream_t s) {
-  const unsigned blocks = (unsigned)(num_cu > 0 ? num_cu * 8 : 2048);
-  hipLaunchKernelGGL(k_eo_list_clear, dim3(blocks), dim3(kListBlock), 0, s, a);
+void eo_begin(const TriArgs& a, uint64_t m, uint32_t* tile_ctr, int num_cu, hipStream_t s) {
+  hipLaunchKernelGGL(k_eo_begin, dim3(eo_blocks(m, 4 * num_cu)), dim3(kListBlock), 0, s, a, m, tile_ctr);
 }
 
-void eo_list_round(const TriArgs& a, int num_cu, hipStream_t s) {
-  const unsigned blocks = (unsigned)(num_cu > 0 ? num_cu * 8 : 2048);
-  hipLaunchKernelGGL(k_eo_list_bid, dim3(blocks), dim3(kListBlock), 0, s, a);
-  hipLaunchKernelGGL(k_eo_list_accept, dim3(blocks), dim3(kListBlock), 0, s, a);
+void eo_list_bids(const TriArgs& a, uint64_t m, int num_cu, hipStream_t s) {
+  hipLaunchKernelGGL(k_eo_list_bid, dim3(eo_blocks(m, num_cu)), dim3(kListBlock), 0, s, a);
+}
+
+void eo_accept(const TriArgs& a, uint64_t m, uint64_t n, int num_cu, hipStream_t s) {
+  hipLaunchKernelGGL(k_eo_accept, dim3(eo_blocks(m > n ? m : n, num_cu)), dim3(kListBlock), 0, s, a, n);
 }
 
 uint64_t tri_tile_max() { return kTT; }

@@ -570,3 +570,21 @@ def test_dag_rows_of_the_register_sorts(slim, k):
     g = gg.from_pairs(n, pairs, f"5xK{k}")
     for op in ("tr", "es"):
         assert_same(gpu_run(slim, g, op, 0.6, 7), oracle_run(g, op, 0.6, 7), f"{g.name} {op}")
+
+
+@pytest.mark.parametrize("per_launch", [1, 3, 16])
+@pytest.mark.parametrize("try_pct", [0, 250, 100000])
+def test_edge_once_rounds_of_small_and_long_lists(slim, per_launch, try_pct):
+    """Edge-Once on graphs whose triangle lists hold from a few records (less
+    than a wave) to more than every wave's span, never started, started and
+    dropped for overflow, with the host looking after every round or never."""
+    old = {k: slim.tune_get(k) for k in ("eo_rounds", "eo_list_try")}
+    try:
+        slim.tune_set("eo_rounds", per_launch)
+        slim.tune_set("eo_list_try", try_pct)
+        for g in (gg.complete(3), gg.friendship(40), gg.complete(40), gg.er(3000, 30.0, 2),
+                  gg.rmat(12, 16, 3), gg.er(60000, 12.0, 5)):
+            assert_same(gpu_run(slim, g, "eotr", 0.7, 9), oracle_run_x(g, "eotr", 0.7, 9), g.name)
+    finally:
+        for k, v in old.items():
+            slim.tune_set(k, v)
