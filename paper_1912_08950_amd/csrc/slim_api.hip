@@ -285,12 +285,20 @@ TriArgs tri_args(const SetShape& S, const SetLayout& L, const Tuning& knobs, voi
   a.tcount = S.has_mc ? at<uint32_t>(ws, L.tcount) : nullptr;
   return a;
 }
+// Up to this many edges the output pass reads the mark bytes themselves (they
+// fit an L2, and packing them is a launch: 53.0 -> 49.5 us for G(2000), no
+// difference at 1.06e6 edges); the bitmap of a larger graph is the smaller
+// gather target (R-MAT scale 20, 1.6e7 edges: 3.43 ms packed, 3.56 ms by
+// bytes).
+constexpr uint64_t kPackMin = 1ull << 20;
+
 // Output CSRs and counters of a set from the marks.
 void finish_set(const SetShape& S, const SetLayout& L, void* ws, const int64_t* row_off,
                 const uint32_t* col, bool tr, hipStream_t s) {
-  uint32_t* del = tr ? at<uint32_t>(ws, L.del) : nullptr;
-  if (tr) pack_marks(at<uint8_t>(ws, L.marks), del, S.NNZ / 2, s);
-  compact_out(row_off, col, tr ? at<uint32_t>(ws, L.eid) : nullptr, del, S.NNZ / 2,
+  uint8_t* marks = tr ? at<uint8_t>(ws, L.marks) : nullptr;
+  uint32_t* del = tr && S.NNZ / 2 > kPackMin ? at<uint32_t>(ws, L.del) : nullptr;
+  if (del) pack_marks(marks, del, S.NNZ / 2, s);
+  compact_out(row_off, col, tr ? at<uint32_t>(ws, L.eid) : nullptr, del, marks, S.NNZ / 2,
               at<GDesc>(ws, L.gd), S.count, at<uint64_t>(ws, L.t0c), at<TileRec>(ws, L.recs_c),
               S.n_c, S.most_c, at<uint32_t>(ws, L.tile_cnt), at<uint64_t>(ws, L.masks),
               at<uint64_t>(ws, L.tile_base), at<uint64_t>(ws, L.scan_tmp),
@@ -486,7 +494,9 @@ int check_call(const slim_graph* g, int op, double p, void* ws, uint64_t ws_byte
   return SLIM_OK;
 }
 
-// The header of a one-graph set, written by one small kernel.
+constexpr int kSmallTile = 512;
+
+// The header of a one-graph set, written by the first launch.
 struct SingleHdr {
   GDesc gd[2];
   uint64_t t0c[2];
@@ -525,6 +535,12 @@ int single_op(int op, const slim_graph* g, double p, uint64_t seed, void* ws, ui
     std::lock_guard<std::mutex> lk(tuning_mutex());
     knobs = tuning();
   }
+  // Few tiles leave blocks idle, and a smaller tile is a shorter chain: half
+  // tiles where whole ones would be at most two per resident block (R-MAT of
+  // 5000 vertices: 86 us with 1024 entries per tile, 76 with 512, 77 with 256;
+  // 40000: 166, 155, 166; 90001, four tiles per block: 259, 264, 310).
+  if (knobs.tri_tile > kSmallTile && S.n_t(knobs.tri_tile) <= 4 * (uint64_t)g->num_cu)
+    knobs.tri_tile = kSmallTile;
   const SetLayout L = set_layout(S);
   SingleHdr h{};
   GDesc& d = h.gd[0];

@@ -111,7 +111,8 @@ void orient(const int64_t* row_off, const uint32_t* col, const uint32_t* rank, u
             hipStream_t s);
 // Output CSRs of every graph of the set: TR graphs keep the entries whose
 // edge is unmarked, ES graphs the entries whose edge is not sampled out.
-// eid/del may be NULL when the set has no TR graph.  masks: kChunks words per
+// eid/marks may be NULL when the set has no TR graph; del, the bitmap of the
+// marks, where the bytes are to be read.  masks: kChunks words per
 // tile (the count pass's ballots, read back by the scatter pass).
 // Packs the per-edge deletion bytes into the bitmap the compaction reads
 // (32 bytes -> one word).
@@ -122,8 +123,8 @@ void pack_marks(const uint8_t* marks, uint32_t* del, uint64_t m, hipStream_t s);
 inline uint32_t out_kind(int op) { return op == SLIM_OP_ES ? 1u : op == SLIM_OP_SPECTRAL ? 2u : 0u; }
 constexpr uint64_t kSelfScan = 8192;
 void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* eid,
-                 const uint32_t* del, uint64_t m, const GDesc* gd, uint32_t count,
-                 const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
+                 const uint32_t* del, const uint8_t* marks, uint64_t m, const GDesc* gd,
+                 uint32_t count, const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
                  uint32_t* tile_cnt, uint64_t* masks, uint64_t* tile_base, uint64_t* scan_tmp,
                  const uint64_t* counters, uint32_t kinds, hipStream_t s);
 void validate_offsets(const int64_t* row_off, uint64_t n, uint64_t nnz, uint32_t* err,

@@ -608,7 +608,8 @@ struct OutPolicy {
   static constexpr bool kOut = true;
   const uint32_t* col;
   const uint32_t* eid;
-  const uint32_t* del;
+  const uint32_t* del;   // deletion marks: a bitmap, or NULL:
+  const uint8_t* marks;  //   a byte per edge
   const int64_t* row_off;
   uint64_t m;
   struct Ctx {
@@ -625,7 +626,10 @@ struct OutPolicy {
   __device__ bool needs_rows(const Ctx& x) const { return mode(x) != 0; }
   __device__ const uint32_t* source(const Ctx& x) const { return mode(x) ? col : eid; }
   __device__ uint32_t fetch(const Ctx& x, uint32_t v) const {
-    if (mode(x) == 0) return v < m ? del[v >> 5] : 0u;  // v >= m only for inputs breaking the contract
+    if (mode(x) == 0) {  // v >= m only for inputs breaking the contract
+      if (!del) return v < m ? (uint32_t)marks[v] << (v & 31u) : 0u;
+      return v < m ? del[v >> 5] : 0u;
+    }
     if (mode(x) == 2) return x.vthr[v - x.vb];
     return 0u;
   }
@@ -856,8 +860,8 @@ void orient(const int64_t* row_off, const uint32_t* col, const uint32_t* rank, u
 }
 
 void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* eid,
-                 const uint32_t* del, uint64_t m, const GDesc* gd, uint32_t count,
-                 const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
+                 const uint32_t* del, const uint8_t* marks, uint64_t m, const GDesc* gd,
+                 uint32_t count, const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,
                  uint32_t* tile_cnt, uint64_t* masks, uint64_t* tile_base, uint64_t* scan_tmp,
                  const uint64_t* counters, uint32_t kinds, hipStream_t s) {
   auto go = [&](auto policy) {
@@ -866,10 +870,10 @@ void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* ei
                                        scan_tmp, counters, s);
   };
   switch (kinds) {
-    case 1u << 0: go(OutPolicy<0>{col, eid, del, row_off, m}); break;
-    case 1u << 1: go(OutPolicy<1>{col, eid, del, row_off, m}); break;
-    case 1u << 2: go(OutPolicy<2>{col, eid, del, row_off, m}); break;
-    default: go(OutPolicy<kMixed>{col, eid, del, row_off, m});
+    case 1u << 0: go(OutPolicy<0>{col, eid, del, marks, row_off, m}); break;
+    case 1u << 1: go(OutPolicy<1>{col, eid, del, marks, row_off, m}); break;
+    case 1u << 2: go(OutPolicy<2>{col, eid, del, marks, row_off, m}); break;
+    default: go(OutPolicy<kMixed>{col, eid, del, marks, row_off, m});
   }
 }
 

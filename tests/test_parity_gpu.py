@@ -588,3 +588,13 @@ def test_edge_once_rounds_of_small_and_long_lists(slim, per_launch, try_pct):
     finally:
         for k, v in old.items():
             slim.tune_set(k, v)
+
+
+@pytest.mark.parametrize("n", [85000, 89000, 172000, 178000])
+def test_sizes_beside_the_small_graph_rules(slim, n):
+    """G(n, 12/n) with CSR entries on both sides of 1024 tiles of 1024 (256
+    CUs) and edges on both sides of 2^20."""
+    g = gg.er(n, 12.0, 4)
+    for op in ("tr", "es"):
+        assert_same(gpu_run(slim, g, op, 0.5, 2), oracle_run(g, op, 0.5, 2), f"er{n} {op}")
+    assert_same(gpu_run(slim, g, "eotr", 0.5, 2), oracle_run_x(g, "eotr", 0.5, 2), f"er{n} eotr")
