@@ -2,7 +2,7 @@
 // section 4.3: every triangle of the input graph runs kernel `p-1-reduction`
 // once; a selected triangle deletes one uniformly chosen edge).
 //
-// Vertices are ranked by (degree, id) and every edge points from lower to
+// Vertices are ranked by degree class and every edge points from lower to
 // higher rank.  A triangle y < x < w (in rank) is found exactly once, from
 // its middle vertex x: the edge (y,x) is an in-edge of x, w lies in out(x)
 // and in out(y) above x.  Work is organised over tiles of CSR entries: the
@@ -12,15 +12,16 @@
 // the sorted row; the scan items of all in-edges of a batch are spread over
 // the lanes, kQuad consecutive ones per lane.
 //
-// What bounds the scan is vector-instruction issue, then LDS traffic, so an
-// item costs as little as possible: one multiply-add, one 4-byte read of a
+// What bounds the scan is vector-instruction issue (on graphs far larger than
+// the L2s also the traffic of the rows: 0.95 of a copy's rate at R-MAT scale
+// 24), then LDS traffic, so an item costs as little as possible: one multiply-add, one 4-byte read of a
 // 65536-bit filter and one bit test.  At scale 24 a quarter of the items are
 // triangles and at most 3% more pass the filter; only those go to a per-wave
 // stack, 64 at a time, for the exact look-up in the hash, the Philox draw of
 // the id-sorted triple and the marks.  Probing the hash itself for every item
 // (two 16-byte LDS reads and four key compares) took 4.08e10 vector
 // instructions and 111.6 ms on that graph; filter, stack and 4-item lanes take
-// 2.78e10 and 81.6 ms.  The in-edge of a lane's quad comes from a bit mask of
+// 2.77e10 and, with the steps noted further down, 79.4 ms.  The in-edge of a lane's quad comes from a bit mask of
 // the in-edge starts (two bit counts) instead of a scalar loop over the
 // boundaries inside a window.
 //
@@ -33,10 +34,10 @@
 // Variants (section 4.3), in the general instantiation of the kernel:
 // Triangle p-2-Reduction marks the two edges other than the drawn one;
 // Min-Count p-1-Reduction first runs a counting pass (its own instantiation:
-// every triangle adds 1 to each of its edges, with
-// LDS counters for (y,x) and (x,w) and a global atomic for (y,w); no hash of
-// the triple) and then marks, in each selected triangle, the edge
-// of fewest triangles (ties: the drawn index among the tied edges).
+// every triangle adds 1 to each of its edges, with LDS counters for (y,x) and
+// (x,w) and a global atomic for (y,w); no hash of the triple) and then marks,
+// in each selected triangle, the edge of fewest triangles (ties: the drawn
+// index among the tied edges).
 //
 // Edge-Once p-1-Reduction (section 4.3 with the conditions of section 6.2)
 // runs in rounds.  Bids (pass 2 of this kernel): every selected triangle
