@@ -415,8 +415,13 @@ int eo_finish(const SetShape& S, const SetLayout& L, const Tuning& knobs, int nu
     last += step;
     more = true;
   }
-  if (more)  // the first compaction saw the marks of the first rounds only
+  if (more) {  // the first compaction saw the marks of the first rounds only
+    // every graph is compacted again, and the first compaction has overwritten
+    // the thresholds of the spectral ones
+    if (S.gathered && (S.kinds & (1u << out_kind(SLIM_OP_SPECTRAL))))
+      spectral_thr(at<GDesc>(ws, L.gd), S.count, at<uint64_t>(ws, L.vt0), S.nvt, row_off, s);
     finish_set(S, L, ws, row_off, col, true, s);
+  }
   return SLIM_OK;
 }
 

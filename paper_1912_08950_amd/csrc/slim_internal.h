@@ -102,6 +102,10 @@ void setup(SetupArgs& a, hipStream_t s);
 void gather(const GDesc* gd, uint32_t count, const uint64_t* vtile0, const uint64_t* etile0,
             uint64_t nvt, uint64_t net, uint64_t N, uint64_t NNZ, int64_t* urow, uint32_t* ucol,
             hipStream_t s);
+// Vertex thresholds of the spectral graphs of a gathered set into their output
+// offsets, where the first output pass has overwritten what gather() wrote.
+void spectral_thr(const GDesc* gd, uint32_t count, const uint64_t* vtile0, uint64_t nvt,
+                  const int64_t* urow, hipStream_t s);
 
 // DAG: dag_col = rank ids of the forward entries, fstart = row starts;
 // rcol[j] = rank of col[j] for every entry.

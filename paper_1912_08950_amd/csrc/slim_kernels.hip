@@ -465,6 +465,30 @@ __global__ __launch_bounds__(kBlock) void k_gather(const GDesc* gd, uint32_t cou
   }
 }
 
+// The thresholds of a gathered set's spectral graphs, as k_gather writes them,
+// from the union's offsets.
+__global__ __launch_bounds__(kBlock) void k_spectral_thr(const GDesc* gd, uint32_t count,
+                                                         const uint64_t* vtile0, uint64_t nvt,
+                                                         const int64_t* urow) {
+  for (uint64_t t = blockIdx.x; t < nvt; t += gridDim.x) {
+    const uint32_t g = graph_of_tile(vtile0, count, t);
+    const GDesc& G = gd[g];
+    if (G.op != SLIM_OP_SPECTRAL) continue;
+    const uint64_t i0 = (t - vtile0[g]) * kTile;
+    const uint64_t i1 = i0 + kTile < G.nv ? i0 + kTile : G.nv;
+    uint32_t* thr = static_cast<uint32_t*>(G.out_row);
+    for (uint64_t i = i0 + threadIdx.x; i < i1; i += kBlock)
+      thr[i] = vertex_thr(G.ups, degree_of(urow, G.vb + i));
+  }
+}
+
+void spectral_thr(const GDesc* gd, uint32_t count, const uint64_t* vtile0, uint64_t nvt,
+                  const int64_t* urow, hipStream_t s) {
+  if (nvt)
+    hipLaunchKernelGGL(k_spectral_thr, dim3((unsigned)(nvt < 65536 ? nvt : 65536)), dim3(kBlock), 0,
+                       s, gd, count, vtile0, nvt, urow);
+}
+
 void gather(const GDesc* gd, uint32_t count, const uint64_t* vtile0, const uint64_t* etile0,
             uint64_t nvt, uint64_t net, uint64_t N, uint64_t NNZ, int64_t* urow, uint32_t* ucol,
             hipStream_t s) {
@@ -596,7 +620,8 @@ struct OrientPolicy {
 // p_ab = min(1, upsilon / min(d_a, d_b)) in double precision (section 4.2.1)
 // and weighs it 1/p_ab.  Written values are local ids.  The count pass reads
 // a spectral graph's vertex thresholds from its output offsets, which the
-// scatter pass then overwrites (R-MAT scale 22: count pass 1.50 ms with the
+// scatter pass then overwrites: a second output pass over the set needs them
+// written again (spectral_thr) (R-MAT scale 22: count pass 1.50 ms with the
 // degrees gathered and divided per entry, 1.17 ms with the thresholds).
 // kMode: the mode of every graph of the set (0 triangle operations, 1 ES, 2
 // spectral), or kMixed: a pass over one kind of graph keeps only that kind's

@@ -104,6 +104,44 @@ def test_batch_spectral_weights(slim):
             assert_same((ro, col, st), oracle_run(g, "tr", p, seed))
 
 
+@pytest.mark.parametrize("use_graph", [True, False])
+@pytest.mark.parametrize("eo_rounds", [1, 16])
+def test_batch_edge_once_beside_spectral(slim, use_graph, eo_rounds):
+    """Edge-Once jobs beside jobs of every other operation, spectral ones with
+    weights among them: where the enqueued rounds do not suffice (K_60 takes 9),
+    every graph of the set is compacted a second time."""
+    from oracle import oracle as O
+    graphs = ([gg.complete(60), gg.complete(200), gg.star(5000), gg.empty(9), gg.rmat(12, 16, 3)]
+              + gg.batch_mix(13, 27, 1000, 9000))
+    ops = ((slim.OP_EOTR, 0.7), (slim.OP_SPECTRAL, 2.5), (slim.OP_ES, 0.4), (slim.OP_SPECTRAL, 40.0),
+           (slim.OP_MCTR, 0.5), (slim.OP_TR, 0.5), (slim.OP_TR2, 0.3))
+    jobs = [(*ops[i % len(ops)], gg.mix_seed(61, i)) for i in range(len(graphs))]
+    b = slim.Batch([slim.Graph.from_csr(g) for g in graphs], jobs)
+    b.set("use_graph", 1 if use_graph else 0)
+    b.set("eo_rounds", eo_rounds)
+    names = {slim.OP_TR2: "tr2", slim.OP_MCTR: "mctr", slim.OP_EOTR: "eotr"}
+    want = []
+    for g, (op, p, seed) in zip(graphs, jobs):
+        if op == slim.OP_SPECTRAL:
+            ro, col, w, st = O.spectral_sparsify(g, p, seed)
+            want.append((ro, col, {"n": g.n, "m_in": g.m, "triangles": 0, "selected": 0,
+                                   "deleted": st["deleted"], "m_out": st["m_out"]}, w))
+        elif op in names:
+            want.append(oracle_run_x(g, names[op], p, seed))
+        else:
+            want.append(oracle_run(g, "tr" if op == slim.OP_TR else "es", p, seed))
+    for r in range(3):
+        b.w_all.fill_(-1.0)
+        b.run()
+        for i, w in enumerate(want):
+            label = f"run {r} graph {i} {graphs[i].name} {jobs[i]}"
+            assert_same(b.result_numpy(i), w[:3], label)
+            if jobs[i][0] == slim.OP_SPECTRAL:
+                c0 = int(b.col_base[i])
+                got = b.w_all[c0:c0 + w[1].size].cpu().numpy()
+                assert np.array_equal(got.view(np.uint32), w[3].view(np.uint32)), label
+
+
 def test_batch_same_graph_many_seeds(slim):
     g = gg.er(2000, 16.0, 1)
     dg = slim.Graph.from_csr(g)
