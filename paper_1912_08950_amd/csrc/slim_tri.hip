@@ -219,7 +219,8 @@ __device__ __forceinline__ bool hfind(const Smem& S, uint32_t w, uint32_t h, uin
 
 // Number of entries of the sorted p[lo .. hi), hi - lo <= 4 * kVecs, that are
 // below x (or equal to it, kEqual), from 16-byte loads aligned to 4 bytes; up
-// to 4 * kVecs entries from lo on are read, inside the workspace.
+// to 4 * kVecs entries from lo on are read, inside the workspace.  (Offsets
+// are compared: lo + 7 wraps for the last positions of 2^32 - 1 edges.)
 typedef uint32_t find4_t __attribute__((ext_vector_type(4), aligned(4)));
 template <int kVecs, bool kEqual>
 __device__ __forceinline__ uint32_t count_below(const uint32_t* p, uint32_t lo, uint32_t hi,
@@ -232,7 +233,7 @@ __device__ __forceinline__ uint32_t count_below(const uint32_t* p, uint32_t lo, 
   for (int k = 0; k < kVecs; ++k)
 #pragma unroll
     for (uint32_t i = 0; i < 4; ++i)
-      n += (lo + 4 * k + i < hi) & (kEqual ? v[k][i] <= x : v[k][i] < x);
+      n += (4 * k + i < hi - lo) & (kEqual ? v[k][i] <= x : v[k][i] < x);
   return n;
 }
 
