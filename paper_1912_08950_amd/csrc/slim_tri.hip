@@ -127,7 +127,8 @@ struct TriSmem {
   uint4 ie_tri[kB];       // {end item, y old id, x old id, row's first position | length << 16}
   uint32_t ie_pre[kB];    // first quad
   uint8_t ie_flag[kB];    // deletion mark of (y,x)
-  uint64_t mask[kM];      // bit i of a window: the next in-edge starts at its quad i + 1
+  uint64_t mask[kM + 2 * kDepth];  // bit i of a window: the next in-edge starts at its quad
+                                   //   i + 1; the words from kM on stay 0
   union {
     uint32_t dpos[kHashCap];  // row start offset at each row's first hashed position, else 0
     uint2 queue[kTW][kQ];     // candidates {w, (in-edge << kItemBits) | item}
@@ -723,13 +724,15 @@ __device__ void tri_batch(TriCtx& C, Smem& S, uint32_t b0, uint32_t b1, bool all
       kcur = lo;
     }
     // loads are issued without a branch, so that the wait for one window
-    // leaves the next one's load in flight; a window past the run's end and
-    // the lanes past the last quad read the first columns (items past the
-    // end fail the look-up's end test)
-    const uint32_t item0 = kQuad * s0, last = we - 1;
+    // leaves the next one's load in flight; a window past the run's end (at
+    // most 2 * kDepth - 1 of them) is the next wave's or has no mask bits, so
+    // that k is an in-edge of the batch, and it and the lanes past the last
+    // quad read the first columns (items past the end fail the look-up's end
+    // test)
+    const uint32_t item0 = kQuad * s0;
     const uint32_t lim = kQuad * (n < we * kWave ? n : we * kWave);
     auto load = [&](uint32_t win, Win& x) {
-      const uint2 m = reinterpret_cast<const uint2*>(S.mask)[win < last ? win : last];
+      const uint2 m = reinterpret_cast<const uint2*>(S.mask)[win];
       const uint32_t k = __builtin_amdgcn_mbcnt_hi(m.y, __builtin_amdgcn_mbcnt_lo(m.x, kcur));
       kcur += __popc(m.x) + __popc(m.y);
       const uint2 sc = S.ie_scan[k];
@@ -887,6 +890,7 @@ __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
   }
   const int tid = threadIdx.x, w = tid / kWave;
   const uint32_t lane = lane_id();
+  if (tid < 2 * kDepth) S.mask[kM + tid] = 0;
   const uint64_t ntiles = a.ntiles;
   uint32_t gcur = 0xffffffffu;
   bool clean = false;  // the LDS of the tile setup and the hash is cleared

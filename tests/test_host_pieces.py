@@ -85,3 +85,98 @@ int main() {
   return 0;
 }
 ''')
+
+
+def test_scan_window_loads_stay_inside_the_in_edges(tmp_path):
+    """The window loads of a scan, windows past the run's end included (three
+    are in flight), read the record of an in-edge of the batch: the first
+    window's in-edge and the mask are set up as tri_batch does, and the
+    records are an array that refuses other indexes."""
+    load = between(source("slim_tri.hip"), "auto load = [&](uint32_t win, Win& x) {", "uint32_t qcnt = 0;")
+    consts = "".join(between(source("slim_tri.hip"), f"constexpr int {c} =", "\n") + "\n"
+                     for c in ("kItemBits", "kDepth"))
+    run_host(tmp_path, r'''
+constexpr uint32_t kWave = 64;
+''' + consts + r'''
+struct uint2 { uint32_t x, y; };
+static uint32_t g_lane;
+static uint32_t __builtin_popc(uint32_t v) { return (uint32_t)__builtin_popcount(v); }
+#define __popc __builtin_popc
+static uint32_t mbcnt(uint32_t m, uint32_t from, uint32_t v) {
+  const uint64_t below = (uint64_t(1) << g_lane) - 1;
+  return v + (uint32_t)__builtin_popcount(m & (uint32_t)(below >> from));
+}
+#define __builtin_amdgcn_mbcnt_lo(m, v) mbcnt(m, 0, v)
+#define __builtin_amdgcn_mbcnt_hi(m, v) mbcnt(m, 32, v)
+struct Records {
+  std::vector<uint2> v;
+  uint2 operator[](uint32_t k) const {
+    if (k >= v.size()) { printf("FAIL in-edge %u of %zu\n", k, v.size()); exit(1); }
+    return v[k];
+  }
+};
+template <int kQuad>
+struct Window {
+  struct vec { uint32_t v[kQuad]; };
+  uint32_t row, rec;
+  vec w;
+};
+template <int kQuad, int kM>
+void drive(const std::vector<uint32_t>& len) {  // items of each in-edge
+  using Win = Window<kQuad>;
+  struct { uint32_t mask[2 * (kM + 2 * kDepth)]; Records ie_scan; } S{};
+  std::vector<uint32_t> pre;
+  uint32_t W = 0;
+  for (uint32_t l : len) {
+    pre.push_back(W);
+    S.ie_scan.v.push_back({0u - kQuad * W, W});
+    W += (l + kQuad - 1) / kQuad;
+  }
+  std::vector<uint32_t> dag(kQuad * W + 4);
+  struct { struct { const uint32_t* dag_col; } a; } C{{dag.data()}};
+  const uint32_t kTW = 8, nk = (uint32_t)pre.size();
+  for (uint32_t s0 = 0; s0 < W; s0 += kM * kWave) {
+    memset(S.mask, 0, sizeof(S.mask));
+    for (uint32_t p : pre)
+      if (p > s0 && p - s0 <= (uint32_t)kM * kWave) S.mask[(p - s0 - 1) >> 5] |= 1u << ((p - s0 - 1) & 31u);
+    const uint32_t n = std::min<uint32_t>(W - s0, kM * kWave), nwin = (n + kWave - 1) / kWave;
+    for (uint32_t w = 0; w < kTW; ++w)
+      for (g_lane = 0; g_lane < kWave; ++g_lane) {
+        uint32_t wi = nwin * w / kTW;
+        const uint32_t we = nwin * (w + 1) / kTW;
+        if (wi >= we) continue;
+        uint32_t kcur = 0;
+        for (uint32_t k = 0; k < nk; ++k)
+          if (pre[k] <= s0 + wi * kWave) kcur = k;
+        const uint32_t item0 = kQuad * s0;
+        const uint32_t lim = kQuad * (n < we * kWave ? n : we * kWave);
+        const uint32_t lane = g_lane;
+''' + load.replace("Smem::kM", "kM") + r'''
+        Win x[kDepth];
+        for (int d = 0; d < kDepth; ++d) load(wi + d, x[d]);
+        for (; wi < we; wi += kDepth)
+          for (int d = 0; d < kDepth; ++d) {
+            if (wi + d < we) {  // the in-edge of the lane's quad
+              const uint32_t q = s0 + (wi + d) * kWave + lane;
+              uint32_t want = 0;
+              for (uint32_t k = 0; k < nk; ++k)
+                if (pre[k] <= q) want = k;
+              if (q < W && x[d].rec >> kItemBits != want) { printf("FAIL window\n"); exit(1); }
+            }
+            load(wi + d + kDepth, x[d]);
+          }
+      }
+  }
+}
+int main() {
+  for (uint32_t n : {1, 2, 63, 64, 65, 350, 384, 512})
+    for (uint32_t l : {1, 3, 4, 5, 17, 64, 300}) {
+      const std::vector<uint32_t> len(n, l);
+      drive<4, 512>(len);
+      drive<4, 256>(len);
+      drive<1, 256>(len);
+    }
+  printf("OK\n");
+  return 0;
+}
+''')
