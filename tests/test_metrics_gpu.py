@@ -90,6 +90,20 @@ def test_degree_kl_at_the_counted_range(slim, n, top):
         assert_kl(float(slim.degree_kl(ta, tb, ws=ws).cpu().item()), a, b, f"n={n} top={top}")
 
 
+def test_degree_kl_result_in_mapped_host_memory(slim):
+    """The result pointer gets one store and is never read: pinned host memory,
+    which a device may write but not atomically update, takes the divergence."""
+    import torch
+    for make in (lambda: gg.star(6000), lambda: gg.rmat(14, 16, 2), lambda: gg.complete(40)):
+        g = make()
+        ro = compressed(slim, g, slim.OP_ES, 0.5, 3)
+        a, b = torch.from_numpy(g.row_off).cuda(), torch.from_numpy(np.asarray(ro)).cuda()
+        out = torch.full((1,), -1.0, dtype=torch.float64).pin_memory()
+        slim.degree_kl(a, b, out=out)
+        torch.cuda.synchronize()
+        assert_kl(float(out[0]), g.row_off, ro, g.name)
+
+
 def test_degree_kl_rmat20_reproducible(slim):
     g = gg.rmat(20, 16, 1)
     ro = compressed(slim, g, slim.OP_EOTR, 0.5, 1)
