@@ -420,6 +420,8 @@ SLIM_API void slim_serve_destroy(slim_server_t* s);
  *   "tri_chunk"          out(x) entries hashed in LDS per pass, 32..2048
  *   "tri_blocks_per_cu"  resident blocks per CU of the triangle kernel, 1..64
  *   "tri_tile"           CSR entries per triangle work tile: 256, 512 or 1024
+ *                        (default 1024; until the key is set, calls on a single
+ *                        graph of few tiles take 512)
  *   "eo_rounds"          Edge-Once rounds enqueued before the host checks
  *                        whether more are needed, 1..64 (default 16)
  *   "eo_list_try"        Edge-Once: a bidding round also writes its undecided

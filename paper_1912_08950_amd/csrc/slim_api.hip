@@ -439,6 +439,7 @@ bool tune_apply(Tuning& t, const char* key, int64_t value) {
         (value & (value - 1)) != 0)
       return false;
     t.tri_tile = (int)value;
+    t.tri_tile_set = true;
   } else if (k == "eo_rounds") {
     if (value < 1 || value > 64) return false;
     t.eo_rounds = (int)value;
@@ -540,12 +541,13 @@ int single_op(int op, const slim_graph* g, double p, uint64_t seed, void* ws, ui
     std::lock_guard<std::mutex> lk(tuning_mutex());
     knobs = tuning();
   }
-  // Few tiles leave blocks idle, and a smaller tile is a shorter chain: half
-  // tiles where whole ones would be at most two per resident block (R-MAT of
-  // 5000 vertices: 86 us with 1024 entries per tile, 76 with 512, 77 with 256;
-  // 40000: 166, 155, 166; 90001, four tiles per block: 259, 264, 310).
-  if (knobs.tri_tile > kSmallTile && S.n_t(knobs.tri_tile) <= 4 * (uint64_t)g->num_cu)
-    knobs.tri_tile = kSmallTile;
+  // Few tiles leave blocks idle, and a smaller tile is a shorter chain: unless
+  // the caller chose the tile, half tiles where whole ones would be at most two
+  // per resident block (R-MAT of 5000 vertices: 86 us with 1024 entries per
+  // tile, 76 with 512, 77 with 256; 40000: 166, 155, 166; 90001, four tiles per
+  // block: 259, 264, 310).
+  const uint64_t resident = (uint64_t)g->num_cu * std::min(knobs.tri_blocks_per_cu, kTriResident);
+  if (!knobs.tri_tile_set && S.n_t(knobs.tri_tile) <= 2 * resident) knobs.tri_tile = kSmallTile;
   const SetLayout L = set_layout(S);
   SingleHdr h{};
   GDesc& d = h.gd[0];

@@ -231,11 +231,14 @@ void eo_begin(const TriArgs& a, uint64_t m, uint32_t* tile_ctr, int num_cu, hipS
 void eo_list_bids(const TriArgs& a, uint64_t m, int num_cu, hipStream_t s);
 void eo_accept(const TriArgs& a, uint64_t m, uint64_t n, int num_cu, hipStream_t s);
 
+// Blocks of the triangle kernel that a CU's LDS holds at a time.
+constexpr int kTriResident = 2;
 // Scheduling knobs; never change results.
 struct Tuning {
   int tri_chunk = 2048;       // out-list entries hashed per pass
   int tri_blocks_per_cu = 2;  // resident blocks of the triangle kernel per CU
   int tri_tile = 1024;        // CSR entries per triangle tile (a power of two, 256..1024)
+  bool tri_tile_set = false;  // the caller chose tri_tile: single graphs keep it too
   int eo_rounds = 16;         // Edge-Once rounds enqueued before the host checks (1..64)
   int eo_list_try = 250;      // Edge-Once: list from a round whose previous undecided count is
                               //   at most this percent of the list capacity (0..100000)

@@ -71,7 +71,7 @@ constexpr int kTB = SLIM_TRI_BLOCK;  // threads per block
 constexpr int kTW = kTB / kWave;     // waves per block
 constexpr int kTT = 1024;            // CSR entries per tile
 constexpr int kEntries = kTT / kTB;  // consecutive tile entries per thread
-constexpr int kWavesPerEU = 2 * kTW / 4;  // two resident blocks per CU (LDS), four SIMDs
+constexpr int kWavesPerEU = kTriResident * kTW / 4;  // four SIMDs per CU
 constexpr int kHashCap = 2048;       // out-list entries hashed per pass
 constexpr int kHashPer = kHashCap / kTB;  // most hashed entries per thread
 constexpr int kPosBits = 11;         // bits of a position in the hashed range
@@ -94,7 +94,7 @@ static_assert(kHashCap <= 2 * kBuckets && kHashCap <= (1 << kPosBits), "a positi
 // instantiation: as many as two blocks per CU allow in LDS; the general and
 // Edge-Once ones also keep per-in-edge counts or bids (larger batches cut
 // the per-batch setup and barriers).
-constexpr int kLdsPerBlock = 160 * 1024 / 2;
+constexpr int kLdsPerBlock = 160 * 1024 / kTriResident;
 template <int kMode>
 constexpr int kBatchOf = kMode == kModePlain ? 512 : (kMode == kModeEO ? 352 : 384);
 template <int kMode>
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
   using Smem =
       std::conditional_t<kGeneral || kCount, TriSmemGeneral<kB, kM, kQuad>,
                          std::conditional_t<kEO, TriSmemEO<kB, kM, kQuad>, TriSmemPlain<kB, kM, kQuad>>>;
-  static_assert(sizeof(Smem) <= kLdsPerBlock, "two blocks per CU share the LDS");
+  static_assert(sizeof(Smem) <= kLdsPerBlock, "the resident blocks of a CU share its LDS");
   __shared__ __align__(16) Smem SS;
   TriSmem<kB, kM, kQuad>& S = SS.s;
   TriCtx C;

@@ -376,6 +376,40 @@ def oracle_run_x(g, name, p, seed):
                      "selected": st["selected"], "deleted": st["deleted"], "m_out": st["m_out"]}
 
 
+@pytest.fixture(scope="module")
+def long_row_graphs():
+    """Graphs with split rows and with tiles of in-edges only, and their results."""
+    graphs = [gg.complete(129), gg.complete(400), wheel(9000), bipartite_plus_matching(3, 300),
+              double_star(1025), gg.rmat(12, 16, 7)]
+    return [(g, {op: oracle_run(g, op, 0.5, 3) if op == "tr" else oracle_run_x(g, op, 0.5, 3)
+                 for op in ("tr", *VARIANTS)}) for g in graphs]
+
+
+@pytest.mark.parametrize("chunk", [32, 2048])
+@pytest.mark.parametrize("tile", [256, 512, 1024])
+def test_tile_size_is_the_one_set(slim, long_row_graphs, tile, chunk):
+    """The tile size that the caller set is the one that runs, also where a
+    single graph has few tiles (the workspace begins with the set's header:
+    two descriptors of 120 bytes and three pairs of tile prefixes, the
+    triangle tiles' in the second)."""
+    old = {k: slim.tune_get(k) for k in ("tri_tile", "tri_chunk")}
+    try:
+        slim.tune_set("tri_tile", tile)
+        slim.tune_set("tri_chunk", chunk)
+        assert slim.tune_get("tri_tile") == tile
+        for g, want in long_row_graphs:
+            dg = slim.Graph.from_csr(g)
+            for name, op in (("tr", slim.OP_TR), ("tr2", slim.OP_TR2), ("mctr", slim.OP_MCTR),
+                             ("eotr", slim.OP_EOTR)):
+                bufs = slim.compress(dg, op, 0.5, 3)
+                assert_same(slim.result_numpy(bufs), want[name], f"{g.name} {name}")
+                tiles = int(bufs.ws[264:272].cpu().numpy().view(np.uint64)[0])
+                assert tiles == -(-g.nnz // tile), f"{g.name} {name}"
+    finally:
+        for k, v in old.items():
+            slim.tune_set(k, v)
+
+
 @pytest.mark.parametrize("name", list(SMALL))
 @pytest.mark.parametrize("variant", list(VARIANTS))
 def test_small_graphs_variants(slim, name, variant):
