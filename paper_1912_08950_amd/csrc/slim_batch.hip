@@ -125,7 +125,7 @@ namespace {
 
 bool same_knobs(const Tuning& a, const Tuning& b) {
   return a.tri_chunk == b.tri_chunk && a.tri_blocks_per_cu == b.tri_blocks_per_cu &&
-         a.tri_tile == b.tri_tile && a.eo_rounds == b.eo_rounds;
+         a.tri_tile == b.tri_tile && a.eo_rounds == b.eo_rounds && a.eo_list_try == b.eo_list_try;
 }
 
 void drop_graph(slim_batch* b) {

@@ -180,3 +180,24 @@ int main() {
   return 0;
 }
 ''')
+
+
+def test_a_captured_batch_is_kept_only_under_the_same_knobs(tmp_path):
+    """Every knob that reaches the captured launches is part of the key under
+    which a batch's capture is replayed."""
+    import re
+    tuning = between(source("slim_internal.h"), "struct Tuning {", "Tuning& tuning();")
+    same = between(source("slim_batch.hip"), "bool same_knobs(", "void drop_graph(")
+    knobs = re.findall(r"^  int (\w+) =", tuning, flags=re.M)
+    assert {"tri_tile", "eo_rounds", "eo_list_try"} <= set(knobs)
+    checks = "".join(f'''
+  {{
+    Tuning a, b;
+    b.{k} = a.{k} + 1;
+    if (same_knobs(a, b) || !same_knobs(b, b)) {{ printf("FAIL {k}\\n"); return 1; }}
+  }}''' for k in knobs)
+    run_host(tmp_path, tuning + same + "int main() {" + checks + '''
+  printf("OK\\n");
+  return 0;
+}
+''')
