@@ -159,7 +159,6 @@ SetLayout set_layout(const SetShape& S) {
     L.counters = c.take<uint64_t>(2 * (uint64_t)S.count);
     L.sort_counts = c.take<uint32_t>(4);
     L.tri_ctr = c.take<uint32_t>(4);
-    if (n > kRankSmall) L.classes = c.take<uint32_t>(2 * kDegClasses);
     if (S.has_eo) {
       L.eo_und = c.take<uint64_t>(kEoMaxRounds + 1);
       L.eo_misc = c.take<uint64_t>(3);
@@ -349,11 +348,13 @@ void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num
     if (S.gathered) u.rec[2] = RecJob{nullptr, 0, S.n_u, (uint64_t)kTile, at<TileRec>(ws, L.recs_u)};
     u.order = at<uint32_t>(ws, L.order);
     u.rank = at<uint32_t>(ws, L.rank);
+    // in the row sort's lists and the DAG ranges, which are written later
+    u.rank_work = rank_work(S.N, at<uint32_t>(ws, L.sort_lists));
     u.fill[0] = FillJob{at<uint4>(ws, L.zero), (L.zero_end - L.zero) / sizeof(uint4), 0u};
   }
   setup(u, s);
   if (tr) {
-    degree_rank(row_off, S.N, at<uint32_t>(ws, L.classes), u.order, u.rank, s);
+    degree_rank(row_off, S.N, S.NNZ, u.rank_work, at<uint32_t>(ws, L.dag_rng), u.order, u.rank, s);
     prof_end(profile, s);
     prof_begin(profile, "orient", s);
     const GDesc* gu = gd + S.count;

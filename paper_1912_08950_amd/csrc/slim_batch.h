@@ -48,7 +48,7 @@ struct SetLayout {
   uint64_t fstart, dag_rng, dag_col, fence, eid, del, sort_lists;
   uint64_t minkey, eo_list;
   // cleared by the setup: [zero, zero_end)
-  uint64_t zero, counters, sort_counts, tri_ctr, classes, eo_und, eo_misc, eo_live, closed, marks,
+  uint64_t zero, counters, sort_counts, tri_ctr, eo_und, eo_misc, eo_live, closed, marks,
       tcount, zero_end;
   uint64_t total;
 };

@@ -55,13 +55,20 @@ uint64_t scan_tmp_elems(uint64_t len);
 template <typename TI>
 void scan_excl(const TI* in, uint64_t len, uint64_t* out, uint64_t* tmp, hipStream_t s);
 
-// Ranks of the vertices by degree class, in rank[] and (inverse) order[];
-// classes: 2 * kDegClasses cleared words (unused up to kRankSmall vertices,
-// which setup() ranks).
-constexpr uint32_t kDegClasses = 2432;
+// Ranks of the vertices by (degree, id), in rank[] and (inverse) order[].  Up to
+// kRankSmall vertices setup() ranks; above, it counts degree classes into the
+// 3n words of a RankWork and degree_rank() does the rest (wide: n words).
 constexpr uint64_t kRankSmall = 4096;
-void degree_rank(const int64_t* row_off, uint64_t n, uint32_t* classes, uint32_t* order,
-                 uint32_t* rank, hipStream_t s);
+struct RankWork {
+  uint32_t blocks;     // each takes `span` consecutive vertices
+  uint64_t span;
+  uint32_t* first;     // first rank of each class, and n
+  uint32_t* total;     // vertices of each class
+  uint32_t* cnt;       // by class and block: vertices, then those in earlier blocks
+};
+RankWork rank_work(uint64_t n, uint32_t* ws);
+void degree_rank(const int64_t* row_off, uint64_t n, uint64_t nnz, const RankWork& r, uint32_t* wide,
+                 uint32_t* order, uint32_t* rank, hipStream_t s);
 
 // Copies up to 512 bytes of host data (descriptors) to device memory by a
 // kernel launch: no host-to-device copy, so it can sit in a captured graph.
@@ -80,7 +87,7 @@ struct FillJob {  // p[0 .. quads) = {v, v, v, v}
 };
 constexpr int kMaxRecs = 3, kMaxFills = 1;
 constexpr int kJobHeader = 0, kJobRank = 1, kJobRecs = 2, kJobFill = kJobRecs + kMaxRecs;
-constexpr int kJobThr = kJobFill + kMaxFills, kSetupJobs = kJobThr + 1;
+constexpr int kJobThr = kJobFill + kMaxFills, kJobHist = kJobThr + 1, kSetupJobs = kJobHist + 1;
 struct SetupArgs {
   uint32_t hdr[96];  // header of a one-graph set, hdr_words long (0: none)
   uint32_t hdr_words;
@@ -90,6 +97,7 @@ struct SetupArgs {
   const GDesc* gd;
   uint32_t* order;  // NULL: no ranks
   uint32_t* rank;
+  RankWork rank_work;  // of more than kRankSmall vertices
   RecJob rec[kMaxRecs];
   FillJob fill[kMaxFills];
   uint32_t* thr;  // spectral keep threshold of each vertex (NULL: none), for upsilon ups

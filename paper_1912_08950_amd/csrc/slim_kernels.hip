@@ -3,7 +3,7 @@
 //
 // Data layout (all in HBM, caller-provided workspace), over the union CSR of
 // the set (n vertices, nnz entries, m = nnz/2 edges):
-//   rank[n], order[n]   union id -> rank id and back; rank order = degree class
+//   rank[n], order[n]   union id -> rank id and back; rank order = (degree, id)
 //   rcol[nnz]           rank id of every CSR column (streamed by the orientation)
 //   dag_col[m]          rank ids of the higher-ranked neighbours, rows laid
 //                       out in union-id row order (a stream compaction of CSR)
@@ -168,37 +168,46 @@ template void scan_excl<uint32_t>(const uint32_t*, uint64_t, uint64_t*, uint64_t
 template void scan_excl<uint64_t>(const uint64_t*, uint64_t, uint64_t*, uint64_t*, hipStream_t);
 
 // ------------------------------------------------------- degree ranking
-// Vertices are ranked by degree class: exact below 1024, then 64 classes per
-// doubling, so that ranks order degrees to within 1/64 of their size.  The
-// order inside a class is whatever the atomics give: every total order of the
-// vertices orients the edges without cycles and finds the same triangles, and
-// the classes keep out-degrees within 2% of the bound of an exact degree
-// order.  A counting sort over at most kDegClasses classes is two passes over
-// the offsets (a histogram, then the ranks; R-MAT scale 24: 0.72 ms for three
-// 8-bit passes of a stable radix sort before), or one block's work for a
-// small graph.
+// Vertices are ranked by degree, those of equal degree by id (a wave takes 64
+// ids at a time in their order, and the LDS serves the lanes of one atomic in
+// theirs).  Any total order finds the same triangles, but the scan items depend on it: where degrees are tied or close
+// and ids follow the graph's parts, as in a complete bipartite graph, this
+// order points every edge the same way and leaves nothing to scan (K_4000,4000
+// with ties in any order: 15.9 ms, 2.1 ms so).
+//
+// A counting sort: degree classes, exact below 1024, then 64 per doubling; a
+// block takes consecutive ids and counts them by class (in the setup), the
+// counts of each class are summed up over the blocks, the block hands out the
+// places in the order of its ids, and a last launch orders the classes that
+// hold several degrees.  Few
+// launches and two passes over the offsets (R-MAT scale 24: 0.72 ms for three
+// 8-bit passes of a stable radix sort before); a small graph is one block's
+// work.
 constexpr uint32_t kDegExact = 1024, kDegExactLog = 10, kDegFine = 64;
+constexpr uint32_t kDegClasses = kDegExact + (32 - kDegExactLog) * kDegFine;
+constexpr uint32_t kRankBlocks = 1024;    // most blocks of the histogram
+constexpr uint32_t kFineBins = 4096;      // degrees of a class that are counted in LDS
 
-__device__ __forceinline__ uint32_t deg_class(uint32_t d) {
+__host__ __device__ inline uint32_t deg_class(uint32_t d) {
   if (d < kDegExact) return d;
-  const uint32_t e = 31 - __clz((int)d);
+  const uint32_t e = 31 - __builtin_clz(d);
   return kDegExact + (e - kDegExactLog) * kDegFine + ((d >> (e - 6)) & (kDegFine - 1));
 }
-static_assert(kDegClasses == kDegExact + (32 - kDegExactLog) * kDegFine, "class of degree 2^32 - 1 is the last");
 
 __device__ __forceinline__ uint32_t degree_of(const int64_t* row_off, uint64_t v) {
   return (uint32_t)(row_off[v + 1] - row_off[v]);
 }
 
-// Exclusive sum of cls[kDegClasses] in LDS, in place, by one block.
-__device__ void class_scan(uint32_t* cls, uint32_t* wtot) {
-  constexpr uint32_t kPer = (kDegClasses + kBlock - 1) / kBlock;
+// Exclusive sum of cls[0 .. n) in LDS, n <= kMax, in place, by one block.
+template <uint32_t kMax>
+__device__ void class_scan(uint32_t* cls, uint32_t n, uint32_t* wtot) {
+  constexpr uint32_t kPer = (kMax + kBlock - 1) / kBlock;
   const uint32_t t = threadIdx.x, w = t / kWave;
   uint32_t v[kPer], s = 0;
 #pragma unroll
   for (uint32_t i = 0; i < kPer; ++i) {
     const uint32_t k = t * kPer + i;
-    v[i] = k < kDegClasses ? cls[k] : 0u;
+    v[i] = k < n ? cls[k] : 0u;
     s += v[i];
   }
   const uint32_t incl = wave_incl_sum32(s);
@@ -209,90 +218,238 @@ __device__ void class_scan(uint32_t* cls, uint32_t* wtot) {
 #pragma unroll
   for (uint32_t i = 0; i < kPer; ++i) {
     const uint32_t k = t * kPer + i;
-    if (k < kDegClasses) cls[k] = run;
+    if (k < n) cls[k] = run;
     run += v[i];
   }
   __syncthreads();
 }
 
-// The ranks of a graph of n <= kRankSmall vertices, by one block.
-__device__ void rank_small(const int64_t* row_off, uint32_t n, uint32_t* order, uint32_t* rank) {
-  __shared__ uint32_t cls[kDegClasses];
-  __shared__ uint32_t wtot[kWavesPerBlock];
-  for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) cls[i] = 0;
+// The ranks of a graph of n <= kRankSmall vertices, by one block: every degree
+// is a class of its own, every wave takes a run of ids.  bin[i][d] has the
+// counts, then the next places, of waves 2i (low half) and 2i + 1 in degree d.
+constexpr uint32_t kSmallBins = (uint32_t)kRankSmall;
+__device__ void rank_small(const int64_t* row_off, uint32_t n, uint32_t* order, uint32_t* rank,
+                           uint32_t (&bin)[2][kSmallBins], uint32_t* wtot) {
+  static_assert(kWavesPerBlock == 4 && kSmallBins < (1u << 16), "two waves' places per word");
+  constexpr uint32_t kSteps = kSmallBins / kBlock;
+  const uint32_t t = threadIdx.x, w = t / kWave, lane = lane_id();
+  const uint32_t steps = (n + kBlock - 1) / kBlock, v0 = w * steps * kWave + lane;
+  uint32_t d[kSteps];
+#pragma unroll
+  for (uint32_t k = 0; k < kSteps; ++k) {
+    const uint32_t v = v0 + k * kWave;
+    d[k] = k < steps && v < n ? min(degree_of(row_off, v), kSmallBins - 1) : kSmallBins;
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < 2 * kSteps; ++k) (&bin[0][0])[k * kBlock + t] = 0;
   __syncthreads();
-  for (uint32_t v = threadIdx.x; v < n; v += kBlock)
-    atomicAdd(&cls[deg_class(degree_of(row_off, v))], 1u);
+  uint32_t* mine = bin[w / 2];
+  const uint32_t shift = 16 * (w & 1);
+#pragma unroll
+  for (uint32_t k = 0; k < kSteps; ++k)
+    if (d[k] < kSmallBins) atomicAdd(&mine[d[k]], 1u << shift);
   __syncthreads();
-  class_scan(cls, wtot);
-  for (uint32_t v = threadIdx.x; v < n; v += kBlock) {
-    const uint32_t x = atomicAdd(&cls[deg_class(degree_of(row_off, v))], 1u);
-    rank[v] = x;
-    order[x] = v;
+  uint32_t c0[kSteps], c1[kSteps], sum = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kSteps; ++k) {
+    c0[k] = bin[0][t * kSteps + k];
+    c1[k] = bin[1][t * kSteps + k];
+    sum += (c0[k] & 0xffffu) + (c0[k] >> 16) + (c1[k] & 0xffffu) + (c1[k] >> 16);
+  }
+  const uint32_t incl = wave_incl_sum32(sum);
+  if (lane == kWave - 1) wtot[w] = incl;
+  __syncthreads();
+  uint32_t run = incl - sum;
+  for (uint32_t i = 0; i < w; ++i) run += wtot[i];
+#pragma unroll
+  for (uint32_t k = 0; k < kSteps; ++k) {
+    const uint32_t s1 = run + (c0[k] & 0xffffu), s2 = s1 + (c0[k] >> 16), s3 = s2 + (c1[k] & 0xffffu);
+    bin[0][t * kSteps + k] = run | (s1 << 16);
+    bin[1][t * kSteps + k] = s2 | (s3 << 16);
+    run = s3 + (c1[k] >> 16);
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t k = 0; k < kSteps; ++k) {
+    if (d[k] >= kSmallBins) continue;
+    const uint32_t x = (atomicAdd(&mine[d[k]], 1u << shift) >> shift) & 0xffffu;
+    rank[v0 + k * kWave] = x;
+    order[x] = v0 + k * kWave;
   }
 }
 
-// Adds the class histogram of the vertices to hist[kDegClasses].
-__global__ __launch_bounds__(kBlock) void k_class_hist(const int64_t* row_off, uint64_t n,
-                                                       uint32_t* hist) {
-  __shared__ uint32_t cls[kDegClasses];
+// 12 n bytes >= 49164 (blocks - 1), of which 20 KB + 9.8 KB a block are used.
+RankWork rank_work(uint64_t n, uint32_t* ws) {
+  const uint64_t tiles = (n + kTile - 1) / kTile;
+  const uint64_t per = (tiles + kRankBlocks - 1) / kRankBlocks;
+  RankWork r{};
+  r.span = per * kTile;
+  r.blocks = (uint32_t)((n + r.span - 1) / r.span);
+  r.first = ws;
+  r.total = ws + kDegClasses + 64;
+  r.cnt = r.total + kDegClasses + 64;
+  return r;
+}
+
+// Block b's class counts, in the LDS words cls.
+__device__ void class_hist(const int64_t* row_off, uint64_t n, const RankWork& r, uint64_t b,
+                           uint32_t* cls) {
   for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) cls[i] = 0;
   __syncthreads();
-  for (uint64_t v = blockIdx.x * (uint64_t)kBlock + threadIdx.x; v < n;
-       v += (uint64_t)gridDim.x * kBlock)
+  const uint64_t v0 = b * r.span, v1 = v0 + r.span < n ? v0 + r.span : n;
+  for (uint64_t v = v0 + threadIdx.x; v < v1; v += kBlock)
     atomicAdd(&cls[deg_class(degree_of(row_off, v))], 1u);
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock)
-    if (cls[i]) atomicAdd(&hist[i], cls[i]);
+    r.cnt[(uint64_t)i * r.blocks + b] = cls[i];
 }
 
-// Ranks from the histogram: a block takes kTile vertices at a time, counts
-// them by class in LDS and takes a run of each class's ranks with one atomic
-// on cur[class].
-__global__ __launch_bounds__(kBlock) void k_rank(const int64_t* row_off, uint64_t n,
-                                                 const uint32_t* hist, uint32_t* cur,
-                                                 uint32_t* order, uint32_t* rank) {
-  __shared__ uint32_t base[kDegClasses], cnt[kDegClasses];
+// The vertices of a class in earlier blocks, in place of its counts, and in all;
+// a wave per class.
+__global__ __launch_bounds__(kBlock) void k_class_sum(RankWork r) {
+  const uint32_t c = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave, lane = lane_id();
+  uint32_t* cnt = r.cnt + (uint64_t)c * r.blocks;
+  uint32_t run = 0;
+  for (uint32_t b0 = 0; b0 < r.blocks; b0 += 4 * kWave) {
+    uint32_t v[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) v[k] = b0 + k * kWave + lane < r.blocks ? cnt[b0 + k * kWave + lane] : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t incl = wave_incl_sum32(v[k]);
+      if (b0 + k * kWave + lane < r.blocks) cnt[b0 + k * kWave + lane] = run + incl - v[k];
+      run += (uint32_t)__builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+  }
+  if (lane == 0) r.total[c] = run;
+}
+static_assert(kDegClasses % kWavesPerBlock == 0, "whole blocks");
+
+// A vertex of a class of one degree gets its rank; the others are laid out by
+// class, in the order of their ids, in `wide`.
+__global__ __launch_bounds__(kBlock) void k_rank(const int64_t* row_off, uint64_t n, RankWork r,
+                                                 uint32_t* order, uint32_t* rank, uint32_t* wide) {
+  __shared__ uint32_t next[kDegClasses];  // the block's next place in each class
+  __shared__ uint32_t place[kWavesPerBlock][kDegClasses];  // and each wave's, in kTile vertices
   __shared__ uint32_t wtot[kWavesPerBlock];
-  for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) base[i] = hist[i];
-  __syncthreads();
-  class_scan(base, wtot);
-  for (uint64_t v0 = blockIdx.x * (uint64_t)kTile; v0 < n; v0 += (uint64_t)gridDim.x * kTile) {
-    for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) cnt[i] = 0;
-    __syncthreads();
-    uint32_t c[kItems], at[kItems];
+  const uint32_t b = blockIdx.x;
+  const uint64_t v0 = b * r.span, v1 = v0 + r.span < n ? v0 + r.span : n;
+  // classes of the next kTile vertices, a run of kTile / 4 per wave
+  uint32_t c[kItems];
+  uint32_t* mine = place[threadIdx.x / kWave];
+  const uint32_t at = threadIdx.x / kWave * (kItems * kWave) + lane_id();
+  auto classes = [&](uint64_t t0) {
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-      const uint64_t v = v0 + (uint64_t)k * kBlock + threadIdx.x;
-      c[k] = v < n ? deg_class(degree_of(row_off, v)) : kDegClasses;
+      const uint64_t v = t0 + at + k * kWave;
+      c[k] = v < v1 ? deg_class(degree_of(row_off, v)) : kDegClasses;
     }
+  };
+  classes(v0);
+  for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) next[i] = r.total[i];
+  __syncthreads();
+  class_scan<kDegClasses>(next, kDegClasses, wtot);
+  for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) {
+    if (b == 0) r.first[i] = next[i];
+    next[i] += r.cnt[(uint64_t)i * r.blocks + b];
+  }
+  if (b == 0 && threadIdx.x == 0) r.first[kDegClasses] = (uint32_t)n;
+  __syncthreads();
+  for (uint64_t t0 = v0; t0 < v1; t0 += kTile) {
+    if (t0 != v0) {
+      classes(t0);
+      __syncthreads();  // the places have been taken
+    }
+    for (uint32_t i = threadIdx.x; i < kWavesPerBlock * kDegClasses; i += kBlock) (&place[0][0])[i] = 0;
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kItems; ++k)
-      at[k] = c[k] < kDegClasses ? atomicAdd(&cnt[c[k]], 1u) : 0u;
+      if (c[k] < kDegClasses) atomicAdd(&mine[c[k]], 1u);
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock)
-      if (cnt[i]) cnt[i] = base[i] + atomicAdd(&cur[i], cnt[i]);
+    for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) {
+      uint32_t run = next[i];
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) {
+        const uint32_t cnt = place[w][i];
+        place[w][i] = run;
+        run += cnt;
+      }
+      next[i] = run;
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-      const uint64_t v = v0 + (uint64_t)k * kBlock + threadIdx.x;
       if (c[k] >= kDegClasses) continue;
-      const uint32_t x = cnt[c[k]] + at[k];
-      rank[v] = x;
-      order[x] = (uint32_t)v;
+      const uint32_t v = (uint32_t)(t0 + at + k * kWave), x = atomicAdd(&mine[c[k]], 1u);
+      if (c[k] < kDegExact) {
+        rank[v] = x;
+        order[x] = v;
+      } else {
+        wide[x] = v;
+      }
     }
-    __syncthreads();
   }
 }
 
-void degree_rank(const int64_t* row_off, uint64_t n, uint32_t* classes, uint32_t* order,
-                 uint32_t* rank, hipStream_t s) {
+// Class kDegExact + blockIdx.x by degree: a counting sort by what the degrees
+// of the class differ in, whose places one wave takes, kItems loads in flight;
+// beyond kFineBins degrees (from 2^19 on, where the class has at most nnz / 2^19
+// vertices) a vertex counts those before it.
+__global__ __launch_bounds__(kBlock) void k_rank_wide(const int64_t* row_off, const uint32_t* first,
+                                                      const uint32_t* wide, uint32_t* order,
+                                                      uint32_t* rank) {
+  __shared__ uint32_t bin[kFineBins];
+  __shared__ uint32_t wtot[kWavesPerBlock];
+  const uint32_t c = kDegExact + blockIdx.x;
+  const uint32_t s = first[c], len = first[c + 1] - s;
+  if (len == 0) return;
+  const uint32_t degrees = 1u << ((c - kDegExact) / kDegFine + kDegExactLog - 6);
+  const uint32_t* in = wide + s;
+  if (degrees > kFineBins) {
+    for (uint32_t i = threadIdx.x; i < len; i += kBlock) {
+      const uint32_t v = in[i], d = degree_of(row_off, v);
+      uint32_t x = s;
+      for (uint32_t k = 0; k < len; ++k) {
+        const uint32_t dk = degree_of(row_off, in[k]);
+        x += dk < d || (dk == d && k < i);
+      }
+      rank[v] = x;
+      order[x] = v;
+    }
+    return;
+  }
+  for (uint32_t i = threadIdx.x; i < degrees; i += kBlock) bin[i] = 0;
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < len; i += kBlock)
+    atomicAdd(&bin[degree_of(row_off, in[i]) & (degrees - 1)], 1u);
+  __syncthreads();
+  class_scan<kFineBins>(bin, degrees, wtot);
+  if (threadIdx.x >= kWave) return;
+  for (uint64_t i0 = threadIdx.x; i0 < len; i0 += kItems * kWave) {
+    uint32_t v[kItems], d[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) v[k] = i0 + k * kWave < len ? in[i0 + k * kWave] : 0u;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) d[k] = degree_of(row_off, v[k]) & (degrees - 1);
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      if (i0 + k * kWave >= len) continue;
+      const uint32_t x = s + atomicAdd(&bin[d[k]], 1u);
+      rank[v[k]] = x;
+      order[x] = v[k];
+    }
+  }
+}
+
+void degree_rank(const int64_t* row_off, uint64_t n, uint64_t nnz, const RankWork& r, uint32_t* wide,
+                 uint32_t* order, uint32_t* rank, hipStream_t s) {
   if (n <= kRankSmall) return;  // ranked by the setup
-  uint64_t g = (n + kTile - 1) / kTile;
-  if (g > 1024) g = 1024;
-  hipLaunchKernelGGL(k_class_hist, dim3((unsigned)g), dim3(kBlock), 0, s, row_off, n, classes);
-  hipLaunchKernelGGL(k_rank, dim3((unsigned)g), dim3(kBlock), 0, s, row_off, n,
-                     (const uint32_t*)classes, classes + kDegClasses, order, rank);
+  hipLaunchKernelGGL(k_class_sum, dim3(kDegClasses / kWavesPerBlock), dim3(kBlock), 0, s, r);
+  hipLaunchKernelGGL(k_rank, dim3(r.blocks), dim3(kBlock), 0, s, row_off, n, r, order, rank, wide);
+  const uint64_t most = nnz < 0xffffffffu ? nnz : 0xffffffffu;  // no degree is larger
+  if (most >= kDegExact)
+    hipLaunchKernelGGL(k_rank_wide, dim3(deg_class((uint32_t)most) + 1 - kDegExact), dim3(kBlock),
+                       0, s, row_off, (const uint32_t*)r.first, (const uint32_t*)wide, order, rank);
 }
 
 // ------------------------------------------------ spectral thresholds
@@ -387,15 +544,20 @@ __device__ __forceinline__ TileRec tile_rec(const int64_t* row_off, uint32_t g, 
 // ------------------------------------------------------------- setup
 // One launch for everything that waits for nothing but the CSR: the header
 // of a one-graph set, tile records, cleared arrays, the ranks of a small
-// graph.  Every job has blocks of its own.
+// graph or the class counts of a larger one.  Every job has blocks of its own.
 __global__ __launch_bounds__(kBlock) void k_setup(SetupArgs a) {
+  __shared__ uint32_t bins[2][kSmallBins];
+  __shared__ uint32_t wtot[kWavesPerBlock];
+  static_assert(kDegClasses <= 2 * kSmallBins, "the classes fit the bins");
   uint32_t job = 0, b = blockIdx.x;
   while (b >= a.nb[job]) b -= a.nb[job++];  // the grid is the sum of nb
   const uint64_t t = b * (uint64_t)kBlock + threadIdx.x, nt = a.nb[job] * (uint64_t)kBlock;
   if (job == kJobHeader) {
     if (threadIdx.x < a.hdr_words) a.hdr_dst[threadIdx.x] = a.hdr[threadIdx.x];
   } else if (job == kJobRank) {
-    rank_small(a.row_off, (uint32_t)a.n, a.order, a.rank);
+    rank_small(a.row_off, (uint32_t)a.n, a.order, a.rank, bins, wtot);
+  } else if (job == kJobHist) {
+    class_hist(a.row_off, a.n, a.rank_work, b, bins[0]);
   } else if (job == kJobThr) {
     for (uint64_t v = t; v < a.n; v += nt) a.thr[v] = vertex_thr(a.ups, degree_of(a.row_off, v));
   } else if (job < kJobFill) {
@@ -427,6 +589,7 @@ void setup(SetupArgs& a, hipStream_t s) {
   for (int i = 0; i < kMaxRecs; ++i) a.nb[kJobRecs + i] = blocks(a.rec[i].ntiles, 4096);
   for (int i = 0; i < kMaxFills; ++i) a.nb[kJobFill + i] = blocks(a.fill[i].quads, 1024);
   a.nb[kJobThr] = a.thr ? blocks(a.n, 4096) : 0;
+  a.nb[kJobHist] = a.order && a.n > kRankSmall ? a.rank_work.blocks : 0;
   uint64_t grid = 0;
   for (int i = 0; i < kSetupJobs; ++i) grid += a.nb[i];
   if (grid) hipLaunchKernelGGL(k_setup, dim3((unsigned)grid), dim3(kBlock), 0, s, a);

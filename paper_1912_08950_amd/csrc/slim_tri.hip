@@ -2,7 +2,7 @@
 // section 4.3: every triangle of the input graph runs kernel `p-1-reduction`
 // once; a selected triangle deletes one uniformly chosen edge).
 //
-// Vertices are ranked by degree class and every edge points from lower to
+// Vertices are ranked by (degree, id) and every edge points from lower to
 // higher rank.  A triangle y < x < w (in rank) is found exactly once, from
 // its middle vertex x: the edge (y,x) is an in-edge of x, w lies in out(x)
 // and in out(y) above x.  Work is organised over tiles of CSR entries: the

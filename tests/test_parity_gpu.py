@@ -606,6 +606,80 @@ def test_dag_rows_of_the_register_sorts(slim, k):
         assert_same(gpu_run(slim, g, op, 0.6, 7), oracle_run(g, op, 0.6, 7), f"{g.name} {op}")
 
 
+def csr_of(n, u, v, name):
+    """CSR of the undirected edges (u, v), given once each."""
+    a, b = np.concatenate([u, v]).astype(np.int64), np.concatenate([v, u]).astype(np.int64)
+    key = np.sort(a * n + b)
+    ro = np.searchsorted(key, np.arange(n + 1, dtype=np.int64) * n).astype(np.int64)
+    return gg.CSR(ro, (key % n).astype(np.uint32), name)
+
+
+def two_parts(a, b, per=None, shuffled=False):
+    """K_{a,b} with the ids of one part before the other's, or (per) every
+    vertex of two equal parts joined to `per` of the other one."""
+    if per is None:
+        u, v = np.repeat(np.arange(a), b), a + np.tile(np.arange(b), a)
+    else:
+        u = np.repeat(np.arange(a), per)
+        v = a + (7 * u + np.tile(np.arange(per) * 1234, a)) % a
+    if shuffled:
+        ids = np.random.default_rng(a).permutation(a + b)
+        u, v = ids[u], ids[v]
+    return csr_of(a + b, u, v, f"parts{a},{b}" + (f"x{per}" if per else "") + "s" * shuffled)
+
+
+def hubs(degrees):
+    """Hubs of the given degrees, joined to one another and to private leaves."""
+    h = len(degrees)
+    u, v = np.triu_indices(h, 1)
+    n = h
+    for i, d in enumerate(degrees):
+        k = d - (h - 1)
+        u = np.concatenate([u, np.full(k, i)])
+        v = np.concatenate([v, np.arange(n, n + k)])
+        n += k
+    return csr_of(n, u, v, "hubs")
+
+
+def dag_out_degrees(bufs, n):
+    """Row lengths of the DAG in a single call's workspace (the second of the
+    header's descriptors, of 120 bytes, has the row starts' address at 88)."""
+    at = int(bufs.ws[208:216].cpu().numpy().view(np.uint64)[0]) - bufs.ws.data_ptr()
+    return np.diff(bufs.ws[at:at + 4 * (n + 1)].cpu().numpy().view(np.uint32).astype(np.int64))
+
+
+@pytest.mark.parametrize("make", [
+    lambda: two_parts(7, 7), lambda: two_parts(60, 60), lambda: two_parts(1500, 1500),
+    lambda: two_parts(2048, 2048), lambda: two_parts(2555, 2555),
+    lambda: two_parts(300, 290, shuffled=True), lambda: two_parts(3000, 2990, shuffled=True),
+    lambda: two_parts(65000, 65000, 16), lambda: two_parts(262001, 262001, 16),
+    lambda: hubs([1100, 1500, 1101, 1499, 1023, 1024, 4300]),
+    lambda: hubs([530300, 530000, 530200, 530100, 600000, 530400]),
+    lambda: gg.rmat(13, 16, 2), lambda: gg.rmat(18, 16, 2)],
+    ids=["K7,7", "K60,60", "K1500,1500", "K2048,2048", "K2555,2555", "K300,290s", "K3000,2990s",
+         "2x65000", "2x262001", "hubs1100", "hubs530000", "rmat13", "rmat18"])
+def test_edges_point_by_degree_and_id(slim, make):
+    """The DAG's row lengths: every edge points to the end of larger degree, of
+    tied ends to that of larger id (one block's ranks, several blocks', with
+    and without a scan, classes of several degrees and of more than are counted
+    in LDS).  Results do not depend on it, the work does."""
+    g = make()
+    dg = slim.Graph.from_csr(g)
+    bufs = slim.compress(dg, slim.OP_TR, 0.5, 3)
+    ro, col, st = slim.result_numpy(bufs)
+    got = dag_out_degrees(bufs, g.n)
+    deg = np.diff(g.row_off)
+    row = np.repeat(np.arange(g.n), deg)
+    dr, dc = deg[row], deg[g.col]
+    assert got.sum() == g.m
+    up = (dc > dr) | ((dc == dr) & (g.col > row))
+    assert np.array_equal(got, np.bincount(row, weights=up, minlength=g.n).astype(np.int64))
+    if g.name.startswith("parts"):  # no triangle
+        assert st["triangles"] == 0 and np.array_equal(ro, g.row_off) and np.array_equal(col, g.col)
+    else:
+        assert_same((ro, col, st), oracle_run(g, "tr", 0.5, 3), g.name)
+
+
 @pytest.mark.parametrize("per_launch", [1, 3, 16])
 @pytest.mark.parametrize("try_pct", [0, 250, 100000])
 def test_edge_once_rounds_of_small_and_long_lists(slim, per_launch, try_pct):
