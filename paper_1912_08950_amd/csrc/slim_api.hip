@@ -363,7 +363,7 @@ void run_set(const SetShape& S, const SetLayout& L, const Tuning& knobs, int num
     orient(row_off, col, u.rank, at<uint32_t>(ws, L.rcol), gu, t0u, at<TileRec>(ws, L.recs_u),
            S.n_u, at<uint32_t>(ws, L.tile_cnt), at<uint64_t>(ws, L.masks),
            at<uint64_t>(ws, L.tile_base), at<uint64_t>(ws, L.scan_tmp), s);
-    sort_rows(fstart, u.rank, S.N, at<uint2>(ws, L.dag_rng), at<uint32_t>(ws, L.dag_col),
+    sort_rows(fstart, u.rank, S.N, S.NNZ / 2, at<uint2>(ws, L.dag_rng), at<uint32_t>(ws, L.dag_col),
               at<uint32_t>(ws, L.fence), at<uint32_t>(ws, L.sort_lists),
               at<uint32_t>(ws, L.sort_counts), num_cu, s);
     prof_end(profile, s);

@@ -150,7 +150,7 @@ void validate_entries(const int64_t* row_off, const uint32_t* col, uint64_t n,
 // row reads the row's samples and then a single line of dag_col.  lists: 3n
 // words, counts: 3 cleared words.
 constexpr uint32_t kFenceStep = 32;
-void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint2* dag_rng,
+void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint64_t m, uint2* dag_rng,
                uint32_t* dag_col, uint32_t* fence, uint32_t* lists, uint32_t* counts, int num_cu,
                hipStream_t s);
 

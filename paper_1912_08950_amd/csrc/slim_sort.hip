@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kLongBlock) void k_sort_long(const uint32_t* fstart
   }
 }
 
-void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint2* dag_rng,
+void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint64_t m, uint2* dag_rng,
                uint32_t* dag_col, uint32_t* fence, uint32_t* lists, uint32_t* counts, int num_cu,
                hipStream_t s) {
   uint32_t* wave_list = lists;
@@ -323,10 +323,15 @@ void sort_rows(const uint32_t* fstart, const uint32_t* rank, uint64_t n, uint2* 
   if (g < 1) g = 1;
   hipLaunchKernelGGL(k_sort_short, dim3((unsigned)g), dim3(kBlock), 0, s, fstart, rank, n, dag_rng,
                      dag_col, fence, wave_list, block_list, huge_list, counts, per);
-  // no more blocks than a small graph can keep busy
+  // a wave for each row that may be listed, two blocks per CU at most (K_1500:
+  // 54 us with n / 32 blocks, half as many, 32 so, 40 with a block for each;
+  // K_1500,1500: 54, 35, 48; G(4000), degree 1000: 40, 24, 30)
+  uint64_t rows = m / (kSortShort + 1);
+  if (rows > n) rows = n;
+  if (rows == 0 || n <= kSortShort) return;  // a row has fewer than n entries
   uint64_t gl = (uint64_t)(num_cu > 0 ? num_cu : 256) * 2;
-  if (gl > n / kSortShort) gl = n / kSortShort;
-  if (gl < 1) return;  // a row has fewer than n entries: none is over kSortShort
+  const uint64_t need = (rows + kLongBlock / kWave - 1) / (kLongBlock / kWave);
+  if (gl > need) gl = need;
   hipLaunchKernelGGL(k_sort_long, dim3((unsigned)gl), dim3(kLongBlock), 0, s, fstart, dag_col,
                      fence, wave_list, block_list, huge_list, counts);
 }
