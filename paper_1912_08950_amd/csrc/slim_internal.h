@@ -133,7 +133,12 @@ void pack_marks(const uint8_t* marks, uint32_t* del, uint64_t m, hipStream_t s);
 // NULL) to its stats.  most_tiles: tiles of the largest graph; kinds: bit
 // out_kind(op) of every graph's operation.
 inline uint32_t out_kind(int op) { return op == SLIM_OP_ES ? 1u : op == SLIM_OP_SPECTRAL ? 2u : 0u; }
-constexpr uint64_t kSelfScan = 8192;
+// Most tiles of a graph whose counts the scatter pass adds up by itself: its
+// loads grow with the square of the tiles, the scan's launches do not (edge
+// sampling of G(n), degree 16, by itself and with the scan: 1024 tiles 28.3 and
+// 31.1 us, 4096 75.1 and 79.6, 6144 100.0 and 100.3, 7168 113.4 and 111.8, 8192
+// 128.2 and 123.4, 32768 641 and 436).
+constexpr uint64_t kSelfScan = 6144;
 void compact_out(const int64_t* row_off, const uint32_t* col, const uint32_t* eid,
                  const uint32_t* del, const uint8_t* marks, uint64_t m, const GDesc* gd,
                  uint32_t count, const uint64_t* tile0, const TileRec* recs, uint64_t ntiles, uint64_t most_tiles,

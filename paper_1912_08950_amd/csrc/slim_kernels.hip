@@ -911,10 +911,10 @@ __device__ __forceinline__ void put_stats(const GDesc* gd, uint32_t count, uint3
 // the graph's last tile, the end offset and the job's counters.  Kept values
 // are gathered in LDS, so that the output is written in whole lines.  Where
 // no graph has more than kSelfScan tiles, a tile adds up the counts of the
-// tiles before it by itself (tile_base is NULL): that is at most 32 loads per
-// thread, and the scan's one to three launches are 4 to 14 us (with the
-// header and the stats as launches too, sampling a 2000-vertex graph took six
-// launches and 29 us; three and 16.6 us now).
+// tiles before it by itself (tile_base is NULL): that is at most 24 loads per
+// thread in place of the scan's one to three launches (with the header and the
+// stats as launches too, sampling a 2000-vertex graph took six launches and 29
+// us; three and 14.8 us now).
 template <class P, typename OffT>
 __global__ __launch_bounds__(kBlock) void k_compact_scatter(
     P p, const int64_t* row_off, const GDesc* gd, uint32_t count, const uint64_t* tile0,
