@@ -64,10 +64,7 @@
 
 namespace slim {
 
-#ifndef SLIM_TRI_BLOCK
-#define SLIM_TRI_BLOCK 512
-#endif
-constexpr int kTB = SLIM_TRI_BLOCK;  // threads per block
+constexpr int kTB = 512;             // threads per block
 constexpr int kTW = kTB / kWave;     // waves per block
 constexpr int kTT = 1024;            // CSR entries per tile
 constexpr int kEntries = kTT / kTB;  // consecutive tile entries per thread
