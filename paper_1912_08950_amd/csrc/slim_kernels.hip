@@ -170,19 +170,20 @@ template void scan_excl<uint64_t>(const uint64_t*, uint64_t, uint64_t*, uint64_t
 // ------------------------------------------------------- degree ranking
 // Vertices are ranked by degree, those of equal degree by id (a wave takes 64
 // ids at a time in their order, and the LDS serves the lanes of one atomic in
-// theirs).  Any total order finds the same triangles, but the scan items depend on it: where degrees are tied or close
-// and ids follow the graph's parts, as in a complete bipartite graph, this
-// order points every edge the same way and leaves nothing to scan (K_4000,4000
-// with ties in any order: 15.9 ms, 2.1 ms so).
+// theirs).  Any total order finds the same triangles, but the scan items depend
+// on it: where degrees are tied or close and ids follow the graph's parts, this
+// order points every edge the same way and leaves nothing to scan (K_4000,4000,
+// p-1: 15.9 ms with ties in any order, 1.9 so; K_3000,2990 with degrees within
+// 1/64 in any order too: 4.5 and 1.3).
 //
 // A counting sort: degree classes, exact below 1024, then 64 per doubling; a
 // block takes consecutive ids and counts them by class (in the setup), the
 // counts of each class are summed up over the blocks, the block hands out the
 // places in the order of its ids, and a last launch orders the classes that
-// hold several degrees.  Few
-// launches and two passes over the offsets (R-MAT scale 24: 0.72 ms for three
-// 8-bit passes of a stable radix sort before); a small graph is one block's
-// work.
+// hold several degrees.  Two passes over the offsets and four launches, the
+// setup among them (R-MAT scale 20: k_class_sum 5 us, k_rank 20, k_rank_wide 7;
+// 90001 vertices: 5, 15 and 5; three 8-bit passes of a stable radix sort took
+// 17 launches and 130 us at scale 20); a small graph is one block's work.
 constexpr uint32_t kDegExact = 1024, kDegExactLog = 10, kDegFine = 64;
 constexpr uint32_t kDegClasses = kDegExact + (32 - kDegExactLog) * kDegFine;
 constexpr uint32_t kRankBlocks = 1024;    // most blocks of the histogram
@@ -313,7 +314,10 @@ __global__ __launch_bounds__(kBlock) void k_class_sum(RankWork r) {
   for (uint32_t b0 = 0; b0 < r.blocks; b0 += 4 * kWave) {
     uint32_t v[4];
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) v[k] = b0 + k * kWave + lane < r.blocks ? cnt[b0 + k * kWave + lane] : 0u;
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t b = b0 + k * kWave + lane;
+      v[k] = b < r.blocks ? cnt[b] : 0u;
+    }
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
       const uint32_t incl = wave_incl_sum32(v[k]);
@@ -740,8 +744,8 @@ __device__ __forceinline__ void load_entries(const uint32_t* src, int64_t j0, ui
 
 // ------------------------------------------------ flag stream compaction
 // Both passes are bound by HBM where nothing is gathered (edge sampling at
-// R-MAT scale 24, 2.1 GB of columns: count 0.95 ms, of which the Philox draws
-// issue for about 0.75, scatter 0.72 ms for 3.2 GB).  What they cost before,
+// R-MAT scale 24, 2.1 GB of columns: count 0.84 ms, of which the Philox draws
+// issue for about 0.75, scatter 0.73 ms for 3.5 GB).  What they cost before,
 // 1.42 and 1.31 ms, was latency: one entry per lane and load, each load
 // behind the last one's store, and a row search of five block barriers.
 //
@@ -784,8 +788,8 @@ struct OrientPolicy {
 // and weighs it 1/p_ab.  Written values are local ids.  The count pass reads
 // a spectral graph's vertex thresholds from its output offsets, which the
 // scatter pass then overwrites: a second output pass over the set needs them
-// written again (spectral_thr) (R-MAT scale 22: count pass 1.50 ms with the
-// degrees gathered and divided per entry, 1.17 ms with the thresholds).
+// written again (spectral_thr).  R-MAT scale 22: count pass 1.50 ms with the
+// degrees gathered and divided per entry, 1.17 ms with the thresholds.
 // kMode: the mode of every graph of the set (0 triangle operations, 1 ES, 2
 // spectral), or kMixed: a pass over one kind of graph keeps only that kind's
 // values in registers (edge sampling at R-MAT scale 24: 1.73 ms with the

@@ -13,17 +13,17 @@
 // the lanes, kQuad consecutive ones per lane.
 //
 // What bounds the scan is vector-instruction issue (on graphs far larger than
-// the L2s also the traffic of the rows: 0.95 of a copy's rate at R-MAT scale
-// 24), then LDS traffic, so an item costs as little as possible: one multiply-add, one 4-byte read of a
-// 65536-bit filter and one bit test.  At scale 24 a quarter of the items are
-// triangles and at most 3% more pass the filter; only those go to a per-wave
-// stack, 64 at a time, for the exact look-up in the hash, the Philox draw of
-// the id-sorted triple and the marks.  Probing the hash itself for every item
-// (two 16-byte LDS reads and four key compares) took 4.08e10 vector
-// instructions and 111.6 ms on that graph; filter, stack and 4-item lanes take
-// 2.77e10 and, with the steps noted further down, 79.4 ms.  The in-edge of a lane's quad comes from a bit mask of
-// the in-edge starts (two bit counts) instead of a scalar loop over the
-// boundaries inside a window.
+// the L2s also the traffic of the rows: 0.85 of a copy's rate at R-MAT scale
+// 24), then LDS traffic, so an item costs as little as possible: one
+// multiply-add, one 4-byte read of a 65536-bit filter and one bit test.  At
+// scale 24 a quarter of the items are triangles and at most 3% more pass the
+// filter; only those go to a per-wave stack, 64 at a time, for the exact look-up
+// in the hash, the Philox draw of the id-sorted triple and the marks.  Probing
+// the hash itself for every item (two 16-byte LDS reads and four key compares)
+// took 4.08e10 vector instructions and 111.6 ms on that graph; filter, stack and
+// 4-item lanes take 2.77e10 and, with the steps noted further down, 79.4 ms.
+// The in-edge of a lane's quad comes from a bit mask of the in-edge starts (two
+// bit counts) instead of a scalar loop over the boundaries inside a window.
 //
 // Deletion marks: (x,w) lies in the tile's own out-lists and (y,x) is an
 // in-edge of the batch: byte flags in LDS; (y,w) is a byte store into
