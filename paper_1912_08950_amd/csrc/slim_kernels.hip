@@ -181,8 +181,8 @@ template void scan_excl<uint64_t>(const uint64_t*, uint64_t, uint64_t*, uint64_t
 // counts of each class are summed up over the blocks, the block hands out the
 // places in the order of its ids, and a last launch orders the classes that
 // hold several degrees.  Two passes over the offsets and four launches, the
-// setup among them (R-MAT scale 20: k_class_sum 5 us, k_rank 20, k_rank_wide 7;
-// 90001 vertices: 5, 15 and 5; three 8-bit passes of a stable radix sort took
+// setup among them (R-MAT scale 20: k_class_sum 5 us, k_rank 16, k_rank_wide 7;
+// 90001 vertices: 5, 11 and 5; three 8-bit passes of a stable radix sort took
 // 17 launches and 130 us at scale 20); a small graph is one block's work.
 constexpr uint32_t kDegExact = 1024, kDegExactLog = 10, kDegFine = 64;
 constexpr uint32_t kDegClasses = kDegExact + (32 - kDegExactLog) * kDegFine;
@@ -334,7 +334,8 @@ static_assert(kDegClasses % kWavesPerBlock == 0, "whole blocks");
 __global__ __launch_bounds__(kBlock) void k_rank(const int64_t* row_off, uint64_t n, RankWork r,
                                                  uint32_t* order, uint32_t* rank, uint32_t* wide) {
   __shared__ uint32_t next[kDegClasses];  // the block's next place in each class
-  __shared__ uint32_t place[kWavesPerBlock][kDegClasses];  // and each wave's, in kTile vertices
+  // and each wave's first one, in kTile vertices
+  __shared__ __align__(16) uint32_t place[kWavesPerBlock][kDegClasses];
   __shared__ uint32_t wtot[kWavesPerBlock];
   const uint32_t b = blockIdx.x;
   const uint64_t v0 = b * r.span, v1 = v0 + r.span < n ? v0 + r.span : n;
@@ -350,28 +351,33 @@ __global__ __launch_bounds__(kBlock) void k_rank(const int64_t* row_off, uint64_
     }
   };
   classes(v0);
-  for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) next[i] = r.total[i];
-  __syncthreads();
-  class_scan<kDegClasses>(next, kDegClasses, wtot);
-  for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) {
-    if (b == 0) r.first[i] = next[i];
-    next[i] += r.cnt[(uint64_t)i * r.blocks + b];
+  constexpr uint32_t kPer = (kDegClasses + kBlock - 1) / kBlock;
+  uint32_t ahead[kPer];  // vertices of the thread's classes in earlier blocks
+#pragma unroll
+  for (uint32_t k = 0; k < kPer; ++k) {
+    const uint32_t i = k * kBlock + threadIdx.x;
+    ahead[k] = i < kDegClasses ? r.cnt[(uint64_t)i * r.blocks + b] : 0u;
+    if (i < kDegClasses) next[i] = r.total[i];
   }
-  if (b == 0 && threadIdx.x == 0) r.first[kDegClasses] = (uint32_t)n;
-  __syncthreads();
   for (uint64_t t0 = v0; t0 < v1; t0 += kTile) {
-    if (t0 != v0) {
-      classes(t0);
-      __syncthreads();  // the places have been taken
-    }
-    for (uint32_t i = threadIdx.x; i < kWavesPerBlock * kDegClasses; i += kBlock) (&place[0][0])[i] = 0;
+    uint4* zero = reinterpret_cast<uint4*>(place);
+    for (uint32_t i = threadIdx.x; i < kWavesPerBlock * kDegClasses / 4; i += kBlock)
+      zero[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    uint32_t nth[kItems];  // of the wave's vertices of its class
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) nth[k] = c[k] < kDegClasses ? atomicAdd(&mine[c[k]], 1u) : 0u;
+    if (t0 == v0) class_scan<kDegClasses>(next, kDegClasses, wtot);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kItems; ++k)
-      if (c[k] < kDegClasses) atomicAdd(&mine[c[k]], 1u);
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < kDegClasses; i += kBlock) {
+    for (uint32_t k = 0; k < kPer; ++k) {
+      const uint32_t i = k * kBlock + threadIdx.x;
+      if (i >= kDegClasses) continue;
       uint32_t run = next[i];
+      if (t0 == v0) {
+        if (b == 0) r.first[i] = run;
+        run += ahead[k];
+      }
 #pragma unroll
       for (int w = 0; w < kWavesPerBlock; ++w) {
         const uint32_t cnt = place[w][i];
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(kBlock) void k_rank(const int64_t* row_off, uint64_
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
       if (c[k] >= kDegClasses) continue;
-      const uint32_t v = (uint32_t)(t0 + at + k * kWave), x = atomicAdd(&mine[c[k]], 1u);
+      const uint32_t v = (uint32_t)(t0 + at + k * kWave), x = mine[c[k]] + nth[k];
       if (c[k] < kDegExact) {
         rank[v] = x;
         order[x] = v;
@@ -392,7 +398,12 @@ __global__ __launch_bounds__(kBlock) void k_rank(const int64_t* row_off, uint64_
         wide[x] = v;
       }
     }
+    if (t0 + kTile < v1) {
+      classes(t0 + kTile);
+      __syncthreads();  // the places have been read
+    }
   }
+  if (b == 0 && threadIdx.x == 0) r.first[kDegClasses] = (uint32_t)n;
 }
 
 // Class kDegExact + blockIdx.x by degree: a counting sort by what the degrees
