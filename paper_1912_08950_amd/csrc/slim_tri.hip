@@ -13,7 +13,7 @@
 // the lanes, kQuad consecutive ones per lane.
 //
 // What bounds the scan is vector-instruction issue (on graphs far larger than
-// the L2s also the traffic of the rows: 0.85 of a copy's rate at R-MAT scale
+// the L2s also the traffic of the rows: 0.86 of a copy's rate at R-MAT scale
 // 24), then LDS traffic, so an item costs as little as possible: one
 // multiply-add, one 4-byte read of a 65536-bit filter and one bit test.  At
 // scale 24 a quarter of the items are triangles and at most 3% more pass the
